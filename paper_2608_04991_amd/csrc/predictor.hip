@@ -20,12 +20,11 @@
 // are bf16.
 //
 // Mapping onto CDNA4.  Decode batches are skinny (B <= 256 rows against
-// weight matrices of up to 4096 x 4096), so the products are weight-streaming:
-// a workgroup owns 16 output columns and a K range, its four wavefronts split
-// that range and sum their accumulators through LDS in a fixed order, and
-// long K ranges are split further across workgroups (partials summed, again
-// in a fixed order, by the row kernel that follows).  Every weight byte is
-// read once per 64 batch rows.
+// weight matrices of up to 8192 x 2048), and a step is a chain of dependent
+// launches of a few microseconds each.  So each product is one launch that
+// sums its whole K inside a workgroup, folds in the residual, and leaves the
+// sums of squares from which the next product forms its own RMSNorm: seven
+// launches a step whatever the batch, six products and the attention.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -40,9 +39,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kW = 64;           // wavefront
-constexpr int kGemmWaves = 4;
-constexpr int kNt = 16;          // output columns per workgroup
-constexpr int kRt = 4;           // 16-row tiles per workgroup (64 batch rows)
 constexpr int kHd = 64;          // channels per head
 constexpr float kEps = 1e-6f;    // RMSNorm
 
@@ -53,235 +49,271 @@ __device__ __forceinline__ uint16_t to_bf(float v) {  // round to nearest even (
 }
 
 // ---------------------------------------------------------------------------
-// C[b][n] = sum_k A[b][k] W[n][k] over one K range, A bf16 [M][K] row-major,
-// W bf16 [N][K] (each output's weights contiguous).  Grid: x = N / 16 column
-// tiles, y = K splits, z = 64-row tiles of the batch.  In one MFMA
-// (16 x 16 x 32) lane l holds A[l % 16][8 (l / 16) + j] and
-// W[n0 + l % 16][8 (l / 16) + j], j < 8, each one 16-byte load, and gets
-// C[4 (l / 16) + r][n0 + l % 16], r < 4.
-enum Epi { kPartial = 0, kStore = 1, kSwiglu = 2, kResidOut = 3 };
+// C[b][n] = sum_k A[b][k] W[n][k].  A workgroup owns a tile of 16 TM batch
+// rows x 16 TN output columns over the whole K, and its KW wavefronts split K
+// in units of 64, so that every operand byte of the tile is loaded once, by one
+// wavefront, with up to Q units in flight.
+//
+// The matrix core wants row l % 16 in lane l, so operands loaded straight into
+// its layout put 16 rows in 16 neighbouring lanes, and the vector memory
+// unit then takes a clock per 16 bytes (35 GB/s per compute unit, measured on
+// 16 x 16 tiles of K = 8192).  Here neighbouring lanes load whole 128-byte
+// lines of a row, and the unit passes through the wavefront's own slice of LDS
+// (no barrier) to reach the layout.  A 16-byte piece (row, step of 32, quarter
+// q) sits at 64 step + 4 (row ^ 2 step) + (q ^ (row / 4)) of its 2 KB block:
+// the writes of 16 lanes and the reads of 16 lanes both touch every bank once.
+// With the weights as the first operand lane l receives output columns
+// n0 + 4 (l / 16) + r, r < 4, of batch row l % 16: one 16-byte access per lane.
+//
+// With no K split across workgroups the tile's epilogue sees finished sums, so
+// the residual stream and its RMSNorm need no launch of their own: the product
+// that forms h (kHidden) adds the residual, stores h and the sum of squares of
+// every (row, 16 columns); the product that consumes it (NORM) sums those of
+// its rows and forms bf16(h / sqrt(mean(h^2) + eps) * gain) on the way to LDS.
+enum Epi { kHidden, kQkv, kGate, kOut };
 
-struct Gemm {
-    const uint16_t* a;   // [M][K] (not read with NORM)
-    const uint16_t* w;   // [N][K]
-    int32_t M, N, K, ksplit;   // K range per split
-    float* out;          // kPartial: [splits][M][N]; kStore: [M][N]
-    uint16_t* out16;     // kSwiglu: [M][N/2]; kResidOut: [M][N]
-    const uint16_t* resid;     // kResidOut: bf16 [M][N] added to the product
-    // NORM (M <= kFuseRows, one K range, K <= kFuseK): the activations are
-    // bf16(h / sqrt(mean(h^2) + eps) * gain), h = nres + sum_s npart[s] added
-    // in order, formed by every workgroup in LDS (the norm of the step's row
-    // kernel, folded into the product that consumes it)
-    const float* nres;      // [M][K], or null
-    const float* npart;     // [nsplits][M][K]
-    int32_t nsplits;
-    const uint16_t* ngain;  // bf16 [K]
-    float* nh;              // [M][K]: h, written by the first workgroup; or null
+struct Prod {
+    const uint16_t* a;      // bf16 [M][K] (without NORM)
+    const float* h;         // fp32 [M][K] (NORM)
+    const float* ssin;      // [M][K / 16] sums of squares of h (NORM)
+    const uint16_t* gain;   // bf16 [K] (NORM)
+    const uint16_t* w;      // bf16 [N][K]
+    int32_t M, N, K;
+    const float* resid;     // kHidden: fp32 [M][N] added to the product, or null
+    float* out;             // kHidden, kQkv: fp32 [M][N]
+    float* ssout;           // kHidden: [M][N / 16]
+    const uint16_t* resid16;// kOut: bf16 [M][N]
+    uint16_t* out16;        // kGate: bf16 [M][N / 2]; kOut: bf16 [M][N]
 };
 
-constexpr int kFuseRows = kGemmWaves;  // batch rows whose norm a product forms itself (one per wavefront)
-constexpr int kFuseK = 2048;           // the widest such row (the model width)
-constexpr int kNormPad = 8;            // bf16 padding per LDS row (spreads the rows over the banks)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <int EPI, bool NORM = false>
-__global__ __launch_bounds__(kW * kGemmWaves) void pred_gemm(Gemm g) {
-    __shared__ f32x4 red[kGemmWaves - 1][kRt][kW];
-    extern __shared__ uint4 an4[];  // NORM: the normalized rows, [M][K + kNormPad] bf16
-    const int lane = threadIdx.x & (kW - 1), w = threadIdx.x / kW;
-    const int n0 = blockIdx.x * kNt, s = blockIdx.y, m0 = blockIdx.z * (kRt * 16);
-    const int kq = g.ksplit / kGemmWaves;                // this wavefront's share (multiple of 32)
-    const int kbeg = s * g.ksplit + w * kq;
-    const int col = n0 + (lane & 15), kl = 8 * (lane >> 4);
-    const uint16_t* wrow = g.w + (size_t)col * g.K + kbeg + kl;
-    f32x4 acc[kRt];
-#pragma unroll
-    for (int r = 0; r < kRt; ++r) acc[r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const bool rows_in[kRt] = {m0 + (lane & 15) < g.M, m0 + 16 + (lane & 15) < g.M, m0 + 32 + (lane & 15) < g.M,
-                               m0 + 48 + (lane & 15) < g.M};
-    // four 32-wide steps at a time: their weight loads (the HBM stream) are
-    // all issued before the first product waits, then the activation tiles
-    // (read by every column tile, so cache hits) step by step
-    bf16x8 bw[4];
-    auto load_w = [&](int k0) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            bw[u] = k0 + 32 * u < kq ? *reinterpret_cast<const bf16x8*>(wrow + k0 + 32 * u)
-                                     : bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    };
-    load_w(0);
-    uint16_t* const an = reinterpret_cast<uint16_t*>(an4);
-    const int pitch = g.K + kNormPad;
-    if constexpr (NORM) {
-        // wavefront w forms row w (while the first weights are in flight):
-        // lane l holds channels 512 i + 8 l .. + 7
-        if (w < g.M) {
-            const int b = w;
-            const bool writer = g.nh && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0;
-            float hv[kFuseK / 512][8];
-            float ss = 0.0f;
-#pragma unroll
-            for (int i = 0; i < kFuseK / 512; ++i) {
-                const int c = 512 * i + 8 * lane;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) hv[i][j] = 0.0f;
-                if (c >= g.K) continue;
-                if (g.nres) {
-                    const float4 r0 = *reinterpret_cast<const float4*>(g.nres + (size_t)b * g.K + c);
-                    const float4 r1 = *reinterpret_cast<const float4*>(g.nres + (size_t)b * g.K + c + 4);
-                    hv[i][0] = r0.x; hv[i][1] = r0.y; hv[i][2] = r0.z; hv[i][3] = r0.w;
-                    hv[i][4] = r1.x; hv[i][5] = r1.y; hv[i][6] = r1.z; hv[i][7] = r1.w;
-                }
-                // the partials four at a time, every load of a group issued
-                // before its adds, which run in split order
-                for (int s0 = 0; s0 < g.nsplits; s0 += 4) {
-                    float4 pp[4][2];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (s0 + u < g.nsplits) {
-                            const float* q = g.npart + ((size_t)(s0 + u) * g.M + b) * g.K + c;
-                            pp[u][0] = *reinterpret_cast<const float4*>(q);
-                            pp[u][1] = *reinterpret_cast<const float4*>(q + 4);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (s0 + u < g.nsplits) {
-                            hv[i][0] = hv[i][0] + pp[u][0].x; hv[i][1] = hv[i][1] + pp[u][0].y;
-                            hv[i][2] = hv[i][2] + pp[u][0].z; hv[i][3] = hv[i][3] + pp[u][0].w;
-                            hv[i][4] = hv[i][4] + pp[u][1].x; hv[i][5] = hv[i][5] + pp[u][1].y;
-                            hv[i][6] = hv[i][6] + pp[u][1].z; hv[i][7] = hv[i][7] + pp[u][1].w;
-                        }
-                    }
-                }
-                if (writer) {
-                    float* q = g.nh + (size_t)b * g.K + c;
-                    *reinterpret_cast<float4*>(q) = make_float4(hv[i][0], hv[i][1], hv[i][2], hv[i][3]);
-                    *reinterpret_cast<float4*>(q + 4) = make_float4(hv[i][4], hv[i][5], hv[i][6], hv[i][7]);
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) ss = ss + hv[i][j] * hv[i][j];
-            }
-            for (int o = kW / 2; o > 0; o >>= 1) ss = ss + __shfl_xor(ss, o);
-            const float inv = 1.0f / __builtin_sqrtf(ss / (float)g.K + kEps);
-#pragma unroll
-            for (int i = 0; i < kFuseK / 512; ++i) {
-                const int c = 512 * i + 8 * lane;
-                if (c >= g.K) continue;
-                const uint4 gw = *reinterpret_cast<const uint4*>(g.ngain + c);
-                const uint32_t gv[4] = {gw.x, gw.y, gw.z, gw.w};
-                uint32_t o[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t lo = to_bf(hv[i][2 * j] * inv * __uint_as_float(gv[j] << 16));
-                    const uint32_t hi = to_bf(hv[i][2 * j + 1] * inv * __uint_as_float(gv[j] & 0xFFFF0000u));
-                    o[j] = lo | (hi << 16);
-                }
-                *reinterpret_cast<uint4*>(an + (size_t)b * pitch + c) = make_uint4(o[0], o[1], o[2], o[3]);
-            }
-        }
-        __syncthreads();
-    }
-    for (int k0 = 0; k0 < kq; k0 += 4 * 32) {
-        if (k0 > 0) load_w(k0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (k0 + 32 * u >= kq) break;
-            const int k = k0 + 32 * u;
-#pragma unroll
-            for (int r = 0; r < kRt; ++r) {
-                bf16x8 av = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-                if constexpr (NORM) {
-                    if (r == 0 && rows_in[0])
-                        av = *reinterpret_cast<const bf16x8*>(an + (size_t)(lane & 15) * pitch + kbeg + kl + k);
-                } else if (rows_in[r]) {
-                    av = *reinterpret_cast<const bf16x8*>(g.a + (size_t)(m0 + 16 * r + (lane & 15)) * g.K + kbeg + kl + k);
-                }
-                acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bw[u], acc[r], 0, 0, 0);
-            }
-        }
-    }
-    // the four wavefronts' sums, added in the order ((w0 + w1) + w2) + w3
-    if (w > 0) {
-#pragma unroll
-        for (int r = 0; r < kRt; ++r) red[w - 1][r][lane] = acc[r];
-    }
-    __syncthreads();
-    if (w != 0) return;
-#pragma unroll
-    for (int r = 0; r < kRt; ++r)
-#pragma unroll
-        for (int v = 0; v < kGemmWaves - 1; ++v) acc[r] = acc[r] + red[v][r][lane];
-#pragma unroll
-    for (int r = 0; r < kRt; ++r) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = m0 + 16 * r + 4 * (lane >> 4) + i;
-            if (row >= g.M) continue;
-            const float v = acc[r][i];
-            if constexpr (EPI == kPartial) {
-                g.out[((size_t)s * g.M + row) * g.N + col] = v;
-            } else if constexpr (EPI == kStore) {
-                g.out[(size_t)row * g.N + col] = v;
-            } else if constexpr (EPI == kResidOut) {
-                g.out16[(size_t)row * g.N + col] = to_bf(bf(g.resid[(size_t)row * g.N + col]) + v);
-            } else {
-                // interleaved rows: column 2j is gate j, 2j + 1 is up j; the
-                // even lane gets its neighbour's up value
-                const float up = __shfl_xor(v, 1);
-                if ((col & 1) == 0) {
-                    const float gate = v;
-                    const float silu = gate / (1.0f + __expf(-gate));
-                    g.out16[(size_t)row * (g.N / 2) + col / 2] = to_bf(silu * up);
-                }
-            }
-        }
-    }
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {  // two bf16, round to nearest even
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-// ---------------------------------------------------------------------------
-// Residual stream update and RMSNorm of one batch row per workgroup:
-// h = resid + sum_s part[s] (s in order), stored fp32, and
-// n = bf16(h / sqrt(mean(h^2) + eps) * gain).
-constexpr int kRowThreads = 256;
+// Orders a wavefront's LDS writes before its later reads by other lanes (LDS
+// executes one wavefront's instructions in order; this keeps the compiler
+// from reordering them).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
-struct RowArgs {
-    const float* resid;  // [M][m] or null
-    const float* part;   // [splits][M][m]
-    int32_t splits, M, m;
-    const uint16_t* gain;  // bf16 [m]
-    float* h;            // [M][m]
-    uint16_t* n;         // bf16 [M][m]
+// 16-byte slot of (row, step, quarter) in a block of 16 rows x 64 channels.
+__device__ __forceinline__ uint32_t slot_of(uint32_t row, uint32_t step, uint32_t q) {
+    return 64u * step + 4u * (row ^ (2u * step)) + (q ^ (row >> 2));
+}
+
+// One unit (64 channels) of a wavefront's operands as loaded.
+template <int TM, int TN, bool NORM>
+struct ProdUnit {
+    u32x4 w[TN][2];                  // 8 rows x 128 bytes each
+    u32x4 a[NORM ? 1 : TM][2];
+    f32x4 h[NORM ? TM : 1][4];       // 4 rows x 256 bytes each
+    u32x2 g;
 };
 
-constexpr int kMaxSplits = 16;  // hidden / 512 and ffn / 512 at their largest
-
-__global__ __launch_bounds__(kRowThreads) void pred_row(RowArgs a) {
-    __shared__ float red[kRowThreads / kW];
-    const int b = blockIdx.x, t = threadIdx.x;
-    float ss = 0.0f;
-    for (int c = t; c < a.m; c += kRowThreads) {
-        // every partial loaded before the first add, then summed in order
-        float pv[kMaxSplits];
+template <int TM, int TN, int KW, int Q, int EPI, bool NORM>
+__global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
+    constexpr int F = TM * TN, FPW = (F + KW - 1) / KW;
+    constexpr int kBlk = 128;  // 16-byte slots per block of 16 rows x 64 channels
+    __shared__ u32x4 stage[KW][(TM + TN) * kBlk];
+    static_assert(F * kW <= (TM + TN) * kBlk, "a wavefront's sums fit in its staging slice");
+    const uint32_t lane = threadIdx.x & (kW - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kW));
+    const int n0 = (int)blockIdx.x * (16 * TN), m0 = (int)blockIdx.y * (16 * TM);
+    const uint32_t lr = lane & 15u, lq = lane >> 4;
+    u32x4* const mine = stage[w];
+    const int units = p.K >> 6;
+    const int u0 = units * w / KW, nu = units * (w + 1) / KW - u0;  // this wavefront's units
+    const uint32_t kb = (uint32_t)u0 * 64u;
+    // rows past the batch repeat the last one and are not stored; eights (with
+    // NORM, fours) of rows wholly past it are not loaded at all
+    auto arow = [&](int r) { return (uint32_t)(r < p.M ? r : p.M - 1); };
+    uint32_t wo[TN][2], ao[TM][NORM ? 4 : 2];
 #pragma unroll
-        for (int s = 0; s < kMaxSplits; ++s) pv[s] = s < a.splits ? a.part[((size_t)s * a.M + b) * a.m + c] : 0.0f;
-        float v = a.resid ? a.resid[(size_t)b * a.m + c] : 0.0f;
+    for (int t = 0; t < TN; ++t)
 #pragma unroll
-        for (int s = 0; s < kMaxSplits; ++s)
-            if (s < a.splits) v = v + pv[s];
-        a.h[(size_t)b * a.m + c] = v;
-        ss = ss + v * v;
+        for (int i = 0; i < 2; ++i)
+            wo[t][i] = (uint32_t)(n0 + 16 * t + 8 * i + (int)(lane >> 3)) * (uint32_t)p.K + kb + 8u * (lane & 7u);
+#pragma unroll
+    for (int r = 0; r < TM; ++r) {
+        if constexpr (NORM) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                ao[r][i] = arow(m0 + 16 * r + 4 * i + (int)(lane >> 4)) * (uint32_t)p.K + kb + 4u * lr;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                ao[r][i] = arow(m0 + 16 * r + 8 * i + (int)(lane >> 3)) * (uint32_t)p.K + kb + 8u * (lane & 7u);
+        }
     }
-    // the sum of squares: a butterfly in each wavefront, then the
-    // wavefronts' sums in order
-    for (int o = kW / 2; o > 0; o >>= 1) ss = ss + __shfl_xor(ss, o);
-    if ((t & (kW - 1)) == 0) red[t / kW] = ss;
-    __syncthreads();
-    float tot = red[0];
+    ProdUnit<TM, TN, NORM> st[Q];
+    auto load = [&](ProdUnit<TM, TN, NORM>& b, int u) {
+        const uint32_t k = (uint32_t)u * 64u;
 #pragma unroll
-    for (int w = 1; w < kRowThreads / kW; ++w) tot = tot + red[w];
-    const float inv = 1.0f / __builtin_sqrtf(tot / (float)a.m + kEps);
-    for (int c = t; c < a.m; c += kRowThreads)
-        a.n[(size_t)b * a.m + c] = to_bf(a.h[(size_t)b * a.m + c] * inv * bf(a.gain[c]));
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) b.w[t][i] = *reinterpret_cast<const u32x4*>(p.w + (wo[t][i] + k));
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+            if constexpr (NORM) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (m0 + 16 * r + 4 * i < p.M) b.h[r][i] = *reinterpret_cast<const f32x4*>(p.h + (ao[r][i] + k));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (m0 + 16 * r + 8 * i < p.M) b.a[r][i] = *reinterpret_cast<const u32x4*>(p.a + (ao[r][i] + k));
+            }
+        }
+        if constexpr (NORM) b.g = *reinterpret_cast<const u32x2*>(p.gain + (kb + k + 4u * lr));
+    };
+#pragma unroll
+    for (int u = 0; u < Q; ++u)
+        if (u < nu) load(st[u], u);
+    // what the epilogue adds to this wavefront's parts of the tile
+    f32x4 rs[FPW];
+    uint2 rs16[FPW];
+#pragma unroll
+    for (int i = 0; i < FPW; ++i) {
+        const int f = w + i * KW, row = m0 + 16 * (f / TN) + (int)lr, col = n0 + 16 * (f % TN) + 4 * (int)lq;
+        rs[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        rs16[i] = make_uint2(0u, 0u);
+        if (f < F && row < p.M) {
+            if (EPI == kHidden && p.resid) rs[i] = *reinterpret_cast<const f32x4*>(p.resid + (size_t)row * p.N + col);
+            if (EPI == kOut) rs16[i] = *reinterpret_cast<const uint2*>(p.resid16 + (size_t)row * p.N + col);
+        }
+    }
+    float inv[TM][4];  // of the rows this lane loads
+    if constexpr (NORM) {
+        // lane l sums every fourth group of four of row l / 4's sums of
+        // squares, then the row's four lanes add theirs
+        const int nq = p.K >> 6;
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+            const f32x4* q = reinterpret_cast<const f32x4*>(p.ssin) + (size_t)arow(m0 + 16 * r + (int)(lane >> 2)) * nq;
+            float t = 0.0f;
+            for (int i = (int)(lane & 3u); i < nq; i += 4) {
+                const f32x4 v = q[i];
+                t = t + ((v[0] + v[1]) + (v[2] + v[3]));
+            }
+            t = t + __shfl_xor(t, 1);
+            t = t + __shfl_xor(t, 2);
+            const float iv = 1.0f / __builtin_sqrtf(t / (float)p.K + kEps);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) inv[r][i] = __shfl(iv, 16 * i + 4 * (int)lq);
+        }
+    }
+    f32x4 acc[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) acc[f] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto put = [&](const ProdUnit<TM, TN, NORM>& b) {
+        const uint32_t c = lane & 7u, r8 = lane >> 3;
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                mine[t * kBlk + slot_of(8u * i + r8, c >> 2, c & 3u)] = b.w[t][i];
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+            if constexpr (NORM) {
+                const float g0 = __uint_as_float(b.g.x << 16), g1 = __uint_as_float(b.g.x & 0xFFFF0000u);
+                const float g2 = __uint_as_float(b.g.y << 16), g3 = __uint_as_float(b.g.y & 0xFFFF0000u);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const f32x4 h = b.h[r][i];
+                    const float iv = inv[r][i];
+                    const u32x2 o = {pack2(h[0] * iv * g0, h[1] * iv * g1), pack2(h[2] * iv * g2, h[3] * iv * g3)};
+                    const uint32_t sl = slot_of(4u * i + lq, lr >> 3, (lr >> 1) & 3u);
+                    reinterpret_cast<u32x2*>(mine + (TN + r) * kBlk)[2u * sl + (lr & 1u)] = o;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    mine[(TN + r) * kBlk + slot_of(8u * i + r8, c >> 2, c & 3u)] = b.a[r][i];
+            }
+        }
+    };
+    auto product = [&]() {
+        wave_sync();
+#pragma unroll
+        for (uint32_t step = 0; step < 2u; ++step) {
+            const uint32_t sl = slot_of(lr, step, lq);
+            bf16x8 wv[TN], av[TM];
+#pragma unroll
+            for (int t = 0; t < TN; ++t) wv[t] = __builtin_bit_cast(bf16x8, mine[t * kBlk + sl]);
+#pragma unroll
+            for (int r = 0; r < TM; ++r) av[r] = __builtin_bit_cast(bf16x8, mine[(TN + r) * kBlk + sl]);
+#pragma unroll
+            for (int r = 0; r < TM; ++r)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+                    acc[r * TN + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[t], av[r], acc[r * TN + t], 0, 0, 0);
+        }
+        wave_sync();
+    };
+    int u = 0;
+    for (; u + 2 * Q <= nu; u += Q) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            put(st[i]);
+            load(st[i], u + Q + i);
+            product();
+        }
+    }
+    for (; u < nu; u += Q) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            if (u + i < nu) {
+                put(st[i]);
+                if (u + Q + i < nu) load(st[i], u + Q + i);
+                product();
+            }
+        }
+    }
+    // the wavefronts' sums, through each one's own slice
+#pragma unroll
+    for (int f = 0; f < F; ++f) reinterpret_cast<f32x4*>(mine)[f * kW + lane] = acc[f];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < FPW; ++i) {
+        const int f = w + i * KW;
+        if (f >= F) return;
+        f32x4 v = reinterpret_cast<const f32x4*>(stage[0])[f * kW + lane];
+#pragma unroll
+        for (int x = 1; x < KW; ++x) v = v + reinterpret_cast<const f32x4*>(stage[x])[f * kW + lane];
+        const int row = m0 + 16 * (f / TN) + (int)lr, col = n0 + 16 * (f % TN) + 4 * (int)lq;
+        const bool in = row < p.M;
+        if constexpr (EPI == kHidden) {
+            v = rs[i] + v;
+            float q = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+            q = q + __shfl_xor(q, 16);
+            q = q + __shfl_xor(q, 32);
+            if (in) {
+                *reinterpret_cast<f32x4*>(p.out + (size_t)row * p.N + col) = v;
+                if (lq == 0) p.ssout[(size_t)row * (p.N >> 4) + (col >> 4)] = q;
+            }
+        } else if constexpr (EPI == kQkv) {
+            if (in) *reinterpret_cast<f32x4*>(p.out + (size_t)row * p.N + col) = v;
+        } else if constexpr (EPI == kOut) {
+            const float o0 = __uint_as_float(rs16[i].x << 16) + v[0];
+            const float o1 = __uint_as_float(rs16[i].x & 0xFFFF0000u) + v[1];
+            const float o2 = __uint_as_float(rs16[i].y << 16) + v[2];
+            const float o3 = __uint_as_float(rs16[i].y & 0xFFFF0000u) + v[3];
+            if (in)
+                *reinterpret_cast<uint2*>(p.out16 + (size_t)row * p.N + col) = make_uint2(pack2(o0, o1), pack2(o2, o3));
+        } else {
+            // interleaved rows: column 2j is gate j, 2j + 1 is up j
+            const float g0 = v[0] / (1.0f + __expf(-v[0])) * v[1];
+            const float g1 = v[2] / (1.0f + __expf(-v[2])) * v[3];
+            if (in) *reinterpret_cast<uint32_t*>(p.out16 + (size_t)row * (p.N / 2) + col / 2) = pack2(g0, g1);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -436,7 +468,8 @@ struct PLayout {
 uint64_t up256(uint64_t v) { return (v + 255u) & ~uint64_t(255); }
 
 bool pcfg_valid(const rac_predictor_config* c) {
-    // (every K range splits into four wavefront shares of whole 32-wide steps)
+    // (every K is a whole number of the products' 64-wide units, every N of
+    // their widest tile of 64 columns)
     return c && c->hidden >= 512 && c->hidden <= 8192 && c->hidden % 512 == 0 && c->model >= 128 &&
            c->model <= 2048 && c->model % 128 == 0 && c->heads >= 1 && c->heads * kHd == c->model &&
            c->ffn >= 128 && c->ffn <= 8192 && c->ffn % 128 == 0 && c->window >= 1 && c->window <= 1024 &&
@@ -461,25 +494,24 @@ PLayout playout(const rac_predictor_config* c) {
     return L;
 }
 
-// K splits of the input projection: K ranges of 512 (4 wavefronts x 128)
-int in_splits(const rac_predictor_config* c) { return c->hidden / 512; }
-int down_splits(const rac_predictor_config* c) { return c->ffn % 512 == 0 ? c->ffn / 512 : 1; }
-
+// The total is part of the interface (callers size the scratch by it, and a
+// smaller one is refused), so it stays what it was when the products left
+// partial sums and the normalized rows in memory: the `spare` bytes.
 struct PWork {
-    uint64_t part, h0, h1, h2, n, qkv, o, gg, total;
+    uint64_t ss, h0, h1, h2, spare, qkv, o, gg, total;
 };
 
 PWork pwork(const rac_predictor_config* c, int B) {
     const uint64_t m = c->model, f = c->ffn;
-    const uint64_t S = (uint64_t)(in_splits(c) > down_splits(c) ? in_splits(c) : down_splits(c));
     PWork W;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { const uint64_t at = o; o = up256(o + bytes); return at; };
-    W.part = take(S * B * m * 4);
+    const uint64_t S = c->ffn % 512 == 0 && c->ffn > c->hidden ? f / 512 : (uint64_t)c->hidden / 512;
+    W.ss = take(S * B * m * 4);  // [B][m / 16] used
     W.h0 = take((uint64_t)B * m * 4);
     W.h1 = take((uint64_t)B * m * 4);
     W.h2 = take((uint64_t)B * m * 4);
-    W.n = take((uint64_t)B * m * 2);
+    W.spare = take((uint64_t)B * m * 2);
     W.qkv = take((uint64_t)B * 3 * m * 4);
     W.o = take((uint64_t)B * m * 2);
     W.gg = take((uint64_t)B * f * 2);
@@ -487,41 +519,44 @@ PWork pwork(const rac_predictor_config* c, int B) {
     return W;
 }
 
-template <int EPI>
-rac_status gemm(const uint16_t* a, const uint16_t* w, int M, int N, int K, int splits, float* out, uint16_t* out16,
-                const uint16_t* resid, hipStream_t st) {
-    Gemm g{a, w, M, N, K, K / splits, out, out16, resid, nullptr, nullptr, 0, nullptr, nullptr};
-    void* args[] = {&g};
-    const dim3 grid((unsigned)(N / kNt), (unsigned)splits, (unsigned)((M + kRt * 16 - 1) / (kRt * 16)));
-    return hipLaunchKernel(reinterpret_cast<const void*>(pred_gemm<EPI>), grid, dim3(kW * kGemmWaves), args, 0, st) ==
-                   hipSuccess
+template <int TM, int TN, int KW, int Q, int EPI, bool NORM>
+rac_status prod_launch(const Prod& p, hipStream_t st) {
+    Prod a = p;
+    void* args[] = {&a};
+    const dim3 grid((unsigned)(p.N / (16 * TN)), (unsigned)((p.M + 16 * TM - 1) / (16 * TM)), 1u);
+    return hipLaunchKernel(reinterpret_cast<const void*>(pred_prod<TM, TN, KW, Q, EPI, NORM>), grid, dim3(kW * KW),
+                           args, 0, st) == hipSuccess
                ? RAC_OK
                : RAC_ERR_HIP;
 }
 
-// The product of the normalized rows h = nres + sum_s npart[s] (one K range,
-// M <= kFuseRows, K <= kFuseK): every workgroup forms the norm in LDS.
-template <int EPI>
-rac_status gemm_norm(const float* nres, const float* npart, int nsplits, const uint16_t* gain, float* nh,
-                     const uint16_t* w, int M, int N, int K, float* out, uint16_t* out16, const uint16_t* resid,
-                     hipStream_t st) {
-    Gemm g{nullptr, w, M, N, K, K, out, out16, resid, nres, npart, nsplits, gain, nh};
-    void* args[] = {&g};
-    const size_t lds = (size_t)M * (size_t)(K + kNormPad) * 2u;
-    return hipLaunchKernel(reinterpret_cast<const void*>(pred_gemm<EPI, true>), dim3((unsigned)(N / kNt), 1u, 1u),
-                           dim3(kW * kGemmWaves), args, lds, st) == hipSuccess
-               ? RAC_OK
-               : RAC_ERR_HIP;
+// The tile of a product: the largest of a few whose workgroups still fill the
+// chip's 256 compute units (three quarters of them), since a larger tile loads
+// fewer bytes per output and a smaller one leaves no unit idle.  Measured one
+// product at a time, us, (TM, TN): 16 x 4096 of K = 512: (1, 1) 3.4, (1, 2)
+// 3.6; 64 x 4096 of 512: (1, 4) 4.5, (1, 1) 5.2, (2, 4) 5.6; 256 x 4096 of 512:
+// (2, 4) 7.9, (4, 4) 9.0, (1, 4) 10.0; 256 x 1024 of 4096: (2, 2) 8.9, (1, 2)
+// 11.2, (1, 1) 15; 256 x 512 of 4096: (1, 2) 6.9, (1, 1) 8.4, (2, 2) 8.8.
+constexpr int64_t kFill = 192;
+
+int64_t tiles(const Prod& p, int tm, int tn) {
+    return (int64_t)((p.M + 16 * tm - 1) / (16 * tm)) * (p.N / (16 * tn));
 }
 
-rac_status row(const float* resid, const float* part, int splits, int M, int m, const uint16_t* gain, float* h,
-               uint16_t* n, hipStream_t st) {
-    RowArgs r{resid, part, splits, M, m, gain, h, n};
-    void* args[] = {&r};
-    return hipLaunchKernel(reinterpret_cast<const void*>(pred_row), dim3((unsigned)M), dim3(kRowThreads), args, 0,
-                           st) == hipSuccess
-               ? RAC_OK
-               : RAC_ERR_HIP;
+// Products onto the model width (few columns, long K).
+rac_status prod_hidden(const Prod& p, hipStream_t st) {
+    if (p.M > 16 && tiles(p, 2, 2) >= kFill) return prod_launch<2, 2, 8, 2, kHidden, false>(p, st);
+    if (tiles(p, 1, 2) >= kFill) return prod_launch<1, 2, 8, 2, kHidden, false>(p, st);
+    return prod_launch<1, 1, 8, 4, kHidden, false>(p, st);
+}
+
+// Products from the normalized model width (many columns, short K).
+template <int EPI>
+rac_status prod_wide(const Prod& p, hipStream_t st) {
+    if (p.M > 16 && tiles(p, 2, 4) >= kFill) return prod_launch<2, 4, 4, 1, EPI, true>(p, st);
+    if (tiles(p, 1, 4) >= kFill) return prod_launch<1, 4, 4, 2, EPI, true>(p, st);
+    if (tiles(p, 1, 2) >= kFill) return prod_launch<1, 2, 4, 2, EPI, true>(p, st);
+    return prod_launch<1, 1, 4, 2, EPI, true>(p, st);
 }
 
 rac_status attention(const rac_predictor_config* cfg, const float* qkv, void* cache, const int32_t* pos, int B,
@@ -584,48 +619,37 @@ rac_status rac_predictor_step(const rac_predictor_config* cfg, const void* weigh
     const uint8_t* wb = static_cast<const uint8_t*>(weights);
     auto wt = [&](uint64_t off) { return reinterpret_cast<const uint16_t*>(wb + off); };
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    float* part = reinterpret_cast<float*>(ws + Wb.part);
+    float* ss = reinterpret_cast<float*>(ws + Wb.ss);  // sums of squares of the residual stream, [B][m / 16]
     float* h0 = reinterpret_cast<float*>(ws + Wb.h0);
     float* h1 = reinterpret_cast<float*>(ws + Wb.h1);
     float* h2 = reinterpret_cast<float*>(ws + Wb.h2);
-    uint16_t* n = reinterpret_cast<uint16_t*>(ws + Wb.n);
     float* qkv = reinterpret_cast<float*>(ws + Wb.qkv);
     uint16_t* o = reinterpret_cast<uint16_t*>(ws + Wb.o);
     uint16_t* gg = reinterpret_cast<uint16_t*>(ws + Wb.gg);
     const uint16_t* x = static_cast<const uint16_t*>(h_prev);
     hipStream_t st = stream;
     rac_status s;
-    const int si = in_splits(cfg), sd = down_splits(cfg);
-    if (B <= kFuseRows && m <= kFuseK) {
-        // small batches: each norm is formed by the product that consumes
-        // it (seven launches instead of ten)
-        if ((s = gemm<kPartial>(x, wt(L.w_in), B, m, d, si, part, nullptr, nullptr, st)) != RAC_OK) return s;
-        if ((s = gemm_norm<kStore>(nullptr, part, si, wt(L.g1), h0, wt(L.w_qkv), B, 3 * m, m, qkv, nullptr, nullptr,
-                                   st)) != RAC_OK)
-            return s;
-        if ((s = attention(cfg, qkv, cache, pos, B, o, st)) != RAC_OK) return s;
-        if ((s = gemm<kPartial>(o, wt(L.w_o), B, m, m, 1, part, nullptr, nullptr, st)) != RAC_OK) return s;
-        if ((s = gemm_norm<kSwiglu>(h0, part, 1, wt(L.g2), h1, wt(L.w_gu), B, 2 * f, m, nullptr, gg, nullptr, st)) !=
-            RAC_OK)
-            return s;
-        if ((s = gemm<kPartial>(gg, wt(L.w_down), B, m, f, sd, part, nullptr, nullptr, st)) != RAC_OK) return s;
-        return gemm_norm<kResidOut>(h1, part, sd, wt(L.g3), nullptr, wt(L.w_out), B, d, m, nullptr,
-                                    static_cast<uint16_t*>(ref_out), x, st);
-    }
-    // h0 = x W_in^T (split K), then n1 = RMSNorm(h0)
-    if ((s = gemm<kPartial>(x, wt(L.w_in), B, m, d, si, part, nullptr, nullptr, st)) != RAC_OK) return s;
-    if ((s = row(nullptr, part, si, B, m, wt(L.g1), h0, n, st)) != RAC_OK) return s;
-    // q, k, v; attention over the window; h1 = h0 + o W_o^T; n2 = RMSNorm(h1)
-    if ((s = gemm<kStore>(n, wt(L.w_qkv), B, 3 * m, m, 1, qkv, nullptr, nullptr, st)) != RAC_OK) return s;
+    Prod p{};
+    p.M = B;
+    // h0 = x W_in^T
+    p.a = x; p.w = wt(L.w_in); p.N = m; p.K = d; p.out = h0; p.ssout = ss;
+    if ((s = prod_hidden(p, st)) != RAC_OK) return s;
+    // q, k, v; attention over the window
+    p.h = h0; p.ssin = ss; p.gain = wt(L.g1); p.w = wt(L.w_qkv); p.N = 3 * m; p.K = m; p.out = qkv;
+    if ((s = prod_wide<kQkv>(p, st)) != RAC_OK) return s;
     if ((s = attention(cfg, qkv, cache, pos, B, o, st)) != RAC_OK) return s;
-    if ((s = gemm<kPartial>(o, wt(L.w_o), B, m, m, 1, part, nullptr, nullptr, st)) != RAC_OK) return s;
-    if ((s = row(h0, part, 1, B, m, wt(L.g2), h1, n, st)) != RAC_OK) return s;
-    // SwiGLU; h2 = h1 + g W_down^T; n3 = RMSNorm(h2)
-    if ((s = gemm<kSwiglu>(n, wt(L.w_gu), B, 2 * f, m, 1, nullptr, gg, nullptr, st)) != RAC_OK) return s;
-    if ((s = gemm<kPartial>(gg, wt(L.w_down), B, m, f, sd, part, nullptr, nullptr, st)) != RAC_OK) return s;
-    if ((s = row(h1, part, sd, B, m, wt(L.g3), h2, n, st)) != RAC_OK) return s;
+    // h1 = h0 + o W_o^T
+    p.a = o; p.w = wt(L.w_o); p.N = m; p.K = m; p.resid = h0; p.out = h1;
+    if ((s = prod_hidden(p, st)) != RAC_OK) return s;
+    // SwiGLU; h2 = h1 + g W_down^T
+    p.h = h1; p.gain = wt(L.g2); p.w = wt(L.w_gu); p.N = 2 * f; p.K = m; p.out16 = gg;
+    if ((s = prod_wide<kGate>(p, st)) != RAC_OK) return s;
+    p.a = gg; p.w = wt(L.w_down); p.N = m; p.K = f; p.resid = h1; p.out = h2;
+    if ((s = prod_hidden(p, st)) != RAC_OK) return s;
     // R = x + n3 W_out^T (bf16)
-    return gemm<kResidOut>(n, wt(L.w_out), B, d, m, 1, nullptr, static_cast<uint16_t*>(ref_out), x, st);
+    p.h = h2; p.gain = wt(L.g3); p.w = wt(L.w_out); p.N = d; p.K = m; p.resid16 = x;
+    p.out16 = static_cast<uint16_t*>(ref_out);
+    return prod_wide<kOut>(p, st);
 }
 
 }  // extern "C"
