@@ -27,9 +27,10 @@
 // launches a step whatever the batch, six products and the attention.
 #include <hip/hip_runtime.h>
 
-#include <cmath>
 #include <stddef.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "rac.h"
 
@@ -317,144 +318,211 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
 }
 
 // ---------------------------------------------------------------------------
-// Attention of one (sequence, head) per wavefront.  Lane d holds channel d of
-// the head: q and k get the rotary position (pairs (2i, 2i + 1) turned by
-// pos * 10000^(-2i/64): the angle formed and reduced in binary64, its sine
-// and cosine in binary32), k and v go to the cache slot
+// Attention of one (sequence, head) per workgroup of NW wavefronts.  Lane d
+// holds channel d of the head while q and k get the rotary position (pairs
+// (2i, 2i + 1) turned by pos * 10000^(-2i/64): the angle formed and reduced in
+// binary64, its sine and cosine in binary32); k and v go to the cache slot
 // pos mod W (bf16), and the output is the softmax-weighted sum of the values
-// of positions max(0, pos - W + 1) .. pos, the current one taken from LDS
-// (it is never read back from memory in the same launch).
+// of positions max(0, pos - W + 1) .. pos (the current one is never read back
+// from memory in the same launch).
 //
-// Scores: lane j takes position first + j (64 positions per pass), its key
-// row (128 bytes) as eight 16-byte loads, against q read from LDS.  Output:
-// lane d sums channels 8 (d % 8) .. 8 (d % 8) + 7 over positions d / 8,
-// d / 8 + 8, ... (one 16-byte load of the value row each), then the eight
-// lanes holding the same channels add their sums.
+// What bounds a launch is its chain of waits, so everything that depends on
+// the position alone is requested at once: the keys and values of the first 64
+// positions, before q is turned.  Lane (t, c) = (l / 8, l % 8) takes channels
+// 8c .. 8c + 7 of positions t, t + 8, ... of a pass: eight neighbouring lanes
+// read a key's 128 bytes, and the score, its exponential and its product with
+// the value stay in the lane (a key a lane instead, with the scores through
+// LDS, measured 6.9 us at batch 256, window 64, 9.3 at batch 16 with 16 heads
+// and window 256).  Every lane keeps a running maximum, starting from the
+// current position's score; lanes, then wavefronts, are brought to a common
+// maximum at the end.  Wavefront w takes cached positions
+// 64 (w + NW i) + [0, 64), i = 0, 1, ...
 struct AttnArgs {
     const float* qkv;    // [B][3m]: q | k | v
     uint16_t* cache;     // [B][W][2][m] bf16
     const int32_t* pos;  // [B]
     int32_t B, m, heads, window;
     uint16_t* o;         // [B][m] bf16
-    double theta[kHd / 2];  // 10000^(-2i/64), i < 32 (binary64, from the host's pow)
 };
 
-__device__ __forceinline__ void widen8(const uint4& v, float* f) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+// 10000^(-2i/64), i < 32.  (In constant memory: as a kernel argument indexed by
+// lane it was a load from the argument segment.)
+__constant__ const double kTheta[kHd / 2] = {
+    1.0, 0.7498942093324559, 0.5623413251903491, 0.4216965034285822,
+    0.31622776601683794, 0.23713737056616552, 0.1778279410038923, 0.1333521432163324,
+    0.1, 0.07498942093324558, 0.05623413251903491, 0.042169650342858224,
+    0.03162277660168379, 0.023713737056616554, 0.01778279410038923, 0.01333521432163324,
+    0.01, 0.007498942093324558, 0.005623413251903491, 0.004216965034285823,
+    0.0031622776601683794, 0.0023713737056616554, 0.0017782794100389228, 0.001333521432163324,
+    0.001, 0.0007498942093324559, 0.0005623413251903491, 0.00042169650342858224,
+    0.00031622776601683794, 0.00023713737056616554, 0.00017782794100389227, 0.0001333521432163324};
+
+__device__ __forceinline__ void widen8(const u32x4& v, float* f) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        f[2 * i] = __uint_as_float(w[i] << 16);
-        f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+        f[2 * i] = __uint_as_float(v[i] << 16);
+        f[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u);
     }
 }
 
-constexpr int kMaxWindow = 1024;
+// Sum over the eight lanes of an aligned block, the same in all of them.
+__device__ __forceinline__ float sum8(float v) {
+    auto dpp = [](float x, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value,
+                                                                     0xF, 0xF, false));
+    };
+    v = v + dpp(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+    v = v + dpp(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+    return v + dpp(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+}
 
-__global__ __launch_bounds__(kW) void pred_attn(AttnArgs a) {
-    const int b = blockIdx.x / a.heads, hh = blockIdx.x % a.heads, d = threadIdx.x;
-    const int32_t p = a.pos[b] < 0 ? 0 : a.pos[b];
+template <int NW>
+__global__ __launch_bounds__(kW * NW) void pred_attn(AttnArgs a) {
+    __shared__ alignas(16) float turned[NW][3][kHd];  // q, and k and v as cached
+    __shared__ float wmax[NW], wden[NW];
+    __shared__ alignas(16) float wout[NW][kHd];
+    const int b = (int)blockIdx.x / a.heads, hh = (int)blockIdx.x % a.heads;
+    const int d = threadIdx.x & (kW - 1), w = (int)(threadIdx.x / kW);
+    using cptr = const __attribute__((address_space(4))) int32_t*;  // read-only in this launch: a scalar load
+    const int32_t pv = ((cptr)a.pos)[b];
     const float* row = a.qkv + (size_t)b * 3 * a.m + hh * kHd;
     float q = row[d], k = row[a.m + d];
     const float v = row[2 * a.m + d];
+    const double theta = kTheta[d >> 1];
+    const int p = pv < 0 ? 0 : pv;
+    const int W = a.window, slot = p % W;
+    const int n = p < W ? p : W - 1;  // cached positions attended, besides the current one
+    const uint32_t rowk = 2u * (uint32_t)a.m;  // cache elements per (sequence, slot)
+    uint16_t* const base = a.cache + (size_t)b * W * rowk + hh * kHd;
+    const int t = d >> 3, c = d & 7;
+    u32x4 kv[8], vv[8];
+    // keys and values of positions j0 + t + 8 u (position j of the n is j + 1
+    // .. n slots back: 0 the oldest)
+    auto load = [&](int j0) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int j = j0 + t + 8 * u;
+            kv[u] = vv[u] = u32x4{0u, 0u, 0u, 0u};
+            if (j < n) {
+                int s = slot - n + j;
+                s = s < 0 ? s + W : s;
+                const uint16_t* r = base + (size_t)s * rowk + 8 * c;
+                kv[u] = *reinterpret_cast<const u32x4*>(r);
+                vv[u] = *reinterpret_cast<const u32x4*>(r + a.m);
+            }
+        }
+    };
+    load(kW * w);
     {
         // the angle pos * theta_i in binary64, reduced to [-pi, pi] there (the
         // product k * 2 pi is exact to far below a binary32 ulp for any int32
         // position), then a binary32 sincos
-        const double th = (double)p * a.theta[d >> 1];
+        const double th = (double)p * theta;
         const double kTwoPi = 6.283185307179586476925;
         const float r = (float)(th - kTwoPi * rint(th / kTwoPi));
-        float sn, c;
-        sincosf(r, &sn, &c);
+        float sn, cs;
+        sincosf(r, &sn, &cs);
         const float qo = __shfl_xor(q, 1), ko = __shfl_xor(k, 1);
         // (a, b) -> (a cos - b sin, a sin + b cos): the even lane holds a
-        q = (d & 1) ? qo * sn + q * c : q * c - qo * sn;
-        k = (d & 1) ? ko * sn + k * c : k * c - ko * sn;
+        q = (d & 1) ? qo * sn + q * cs : q * cs - qo * sn;
+        k = (d & 1) ? ko * sn + k * cs : k * cs - ko * sn;
     }
     const uint16_t kb = to_bf(k), vb = to_bf(v);
-    const int slot = p % a.window;
-    const size_t rowk = (size_t)2 * a.m;  // cache elements per (sequence, slot)
-    uint16_t* const base = a.cache + (size_t)b * a.window * rowk + hh * kHd;
-    base[(size_t)slot * rowk + d] = kb;
-    base[(size_t)slot * rowk + a.m + d] = vb;
-    const int first = p - a.window + 1 < 0 ? 0 : p - a.window + 1;
-    const int n = p - first + 1;
-    __shared__ float qs[kHd], sc[kMaxWindow];
-    __shared__ alignas(16) uint16_t kcur[kHd], vcur[kHd];
-    qs[d] = q;
-    kcur[d] = kb;
-    vcur[d] = vb;
-    __syncthreads();
-    float mx = -INFINITY;
-    for (int j0 = 0; j0 < n; j0 += kW) {
-        const int j = j0 + d;
-        if (j < n) {
-            const int pp = first + j;
-            const uint4* kr = pp == p ? reinterpret_cast<const uint4*>(kcur)
-                                      : reinterpret_cast<const uint4*>(base + (size_t)(pp % a.window) * rowk);
-            uint4 kv[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) kv[i] = kr[i];
-            float acc = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float kf[8];
-                widen8(kv[i], kf);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc = acc + qs[8 * i + e] * kf[e];
-            }
-            const float sdot = acc * 0.125f;  // 1 / sqrt(64)
-            sc[j] = sdot;
-            mx = __builtin_fmaxf(mx, sdot);
-        }
+    if (w == 0) {
+        uint16_t* const cur = base + (size_t)slot * rowk;
+        cur[d] = kb;
+        cur[a.m + d] = vb;
     }
-    for (int o = 1; o < kW; o <<= 1) mx = __builtin_fmaxf(mx, __shfl_xor(mx, o));
-    __syncthreads();
-    float den = 0.0f;
-    for (int j = d; j < n; j += kW) {
-        const float e = __expf(sc[j] - mx);
-        sc[j] = e;
-        den = den + e;
-    }
-    for (int o = 1; o < kW; o <<= 1) den = den + __shfl_xor(den, o);
-    __syncthreads();
-    const int t = d >> 3, cb = d & 7;
-    float acc[8];
+    // (each wavefront through its own copy: no barrier)
+    turned[w][0][d] = q;
+    turned[w][1][d] = bf(kb);
+    turned[w][2][d] = bf(vb);
+    wave_sync();
+    float qf[8], acc[8];
+    float mx = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-    // positions t, t + 8, ...: eight value rows loaded before any is added
-    // (the sums run in that order)
-    for (int j0 = t; j0 < n; j0 += 64) {
-        uint4 vv[8];
+    for (int i = 0; i < 8; ++i) {
+        qf[i] = turned[w][0][8 * c + i];
+        mx = mx + qf[i] * turned[w][1][8 * c + i];
+        acc[i] = turned[w][2][8 * c + i];
+    }
+    // the current position is the first term of lanes (0, c) of wavefront 0
+    const bool first = w == 0 && t == 0;
+    mx = sum8(mx) * 0.125f;  // 1 / sqrt(64)
+    float den = first ? 1.0f : 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = first ? acc[i] : 0.0f;
+    for (int j0 = kW * w; j0 < n; j0 += kW * NW) {
+        if (j0 != kW * w) load(j0);
+        float sc[8];
+        float m = mx;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int j = j0 + 8 * u, pp = first + j;
-            vv[u] = j >= n ? uint4{0u, 0u, 0u, 0u}
-                  : pp == p ? reinterpret_cast<const uint4*>(vcur)[cb]
-                            : reinterpret_cast<const uint4*>(base + (size_t)(pp % a.window) * rowk + a.m)[cb];
+            float f[8];
+            widen8(kv[u], f);
+            float s = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s = s + qf[i] * f[i];
+            s = sum8(s) * 0.125f;
+            sc[u] = j0 + t + 8 * u < n ? s : -INFINITY;
+            m = __builtin_fmaxf(m, sc[u]);
         }
+        const float keep = __expf(mx - m);
+        mx = m;
+        den = den * keep;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = acc[i] * keep;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int j = j0 + 8 * u;
-            if (j >= n) break;
-            float vf[8];
-            widen8(vv[u], vf);
-            const float w = sc[j];
+            const float e = __expf(sc[u] - m);
+            den = den + e;
+            float f[8];
+            widen8(vv[u], f);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] = acc[e] + w * vf[e];
+            for (int i = 0; i < 8; ++i) acc[i] = acc[i] + e * f[i];
         }
     }
+    // the eight lanes of every channel block, then the wavefronts
+    float m = mx;
+    for (int o = 8; o < kW; o <<= 1) m = __builtin_fmaxf(m, __shfl_xor(m, o));
+    if constexpr (NW > 1) {
+        if (d == 0) wmax[w] = m;
+        __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        acc[e] = acc[e] + __shfl_xor(acc[e], 8);
-        acc[e] = acc[e] + __shfl_xor(acc[e], 16);
-        acc[e] = acc[e] + __shfl_xor(acc[e], 32);
+        for (int x = 0; x < NW; ++x) m = __builtin_fmaxf(m, wmax[x]);
+    }
+    const float keep = __expf(mx - m);
+    den = den * keep;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = acc[i] * keep;
+    for (int o = 8; o < kW; o <<= 1) {
+        den = den + __shfl_xor(den, o);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = acc[i] + __shfl_xor(acc[i], o);
+    }
+    if constexpr (NW > 1) {
+        if (d == 0) wden[w] = den;
+        if (t == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) wout[w][8 * c + i] = acc[i];
+        }
+        __syncthreads();
+        if (w != 0) return;
+        den = wden[0];
+#pragma unroll
+        for (int x = 1; x < NW; ++x) den = den + wden[x];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            acc[i] = wout[0][8 * c + i];
+#pragma unroll
+            for (int x = 1; x < NW; ++x) acc[i] = acc[i] + wout[x][8 * c + i];
+        }
     }
     if (t == 0) {
-        uint32_t w[4];
+        u32x4 o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[i] = (uint32_t)to_bf(acc[2 * i] / den) | ((uint32_t)to_bf(acc[2 * i + 1] / den) << 16);
-        reinterpret_cast<uint4*>(a.o + (size_t)b * a.m + hh * kHd)[cb] = uint4{w[0], w[1], w[2], w[3]};
+        for (int i = 0; i < 4; ++i) o[i] = pack2(acc[2 * i] / den, acc[2 * i + 1] / den);
+        *reinterpret_cast<u32x4*>(a.o + (size_t)b * a.m + hh * kHd + 8 * c) = o;
     }
 }
 
@@ -559,15 +627,23 @@ rac_status prod_wide(const Prod& p, hipStream_t st) {
     return prod_launch<1, 1, 4, 2, EPI, true>(p, st);
 }
 
-rac_status attention(const rac_predictor_config* cfg, const float* qkv, void* cache, const int32_t* pos, int B,
-                     uint16_t* o, hipStream_t st) {
-    AttnArgs a{qkv, static_cast<uint16_t*>(cache), pos, B, cfg->model, cfg->heads, cfg->window, o, {}};
-    for (int i = 0; i < kHd / 2; ++i) a.theta[i] = std::pow(10000.0, -2.0 * i / kHd);
-    void* args[] = {&a};
-    return hipLaunchKernel(reinterpret_cast<const void*>(pred_attn), dim3((unsigned)(B * cfg->heads)), dim3(kW), args,
-                           0, st) == hipSuccess
+template <int NW>
+rac_status attention_launch(const AttnArgs& args, hipStream_t st) {
+    AttnArgs a = args;
+    void* p[] = {&a};
+    return hipLaunchKernel(reinterpret_cast<const void*>(pred_attn<NW>), dim3((unsigned)(a.B * a.heads)),
+                           dim3(kW * NW), p, 0, st) == hipSuccess
                ? RAC_OK
                : RAC_ERR_HIP;
+}
+
+// As many wavefronts as the window has passes of 64 positions, up to four.
+rac_status attention(const rac_predictor_config* cfg, const float* qkv, void* cache, const int32_t* pos, int B,
+                     uint16_t* o, hipStream_t st) {
+    const AttnArgs a{qkv, static_cast<uint16_t*>(cache), pos, B, cfg->model, cfg->heads, cfg->window, o};
+    if (cfg->window <= kW + 1) return attention_launch<1>(a, st);
+    if (cfg->window <= 2 * kW + 1) return attention_launch<2>(a, st);
+    return attention_launch<4>(a, st);
 }
 
 bool al(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
