@@ -51,7 +51,7 @@ __device__ __forceinline__ uint16_t to_bf(float v) {  // round to nearest even (
 
 // ---------------------------------------------------------------------------
 // C[b][n] = sum_k A[b][k] W[n][k].  A workgroup owns a tile of 16 TM batch
-// rows x 16 TN output columns over the whole K, and its KW wavefronts split K
+// rows x 16 TN output columns (COLS TN) over the whole K, and its KW wavefronts split K
 // in units of 64, so that every operand byte of the tile is loaded once, by one
 // wavefront, with up to Q units in flight.
 //
@@ -69,20 +69,21 @@ __device__ __forceinline__ uint16_t to_bf(float v) {  // round to nearest even (
 // With no K split across workgroups the tile's epilogue sees finished sums, so
 // the residual stream and its RMSNorm need no launch of their own: the product
 // that forms h (kHidden) adds the residual, stores h and the sum of squares of
-// every (row, 16 columns); the product that consumes it (NORM) sums those of
+// every (row, COLS columns); the product that consumes it (NORM) sums those of
 // its rows and forms bf16(h / sqrt(mean(h^2) + eps) * gain) on the way to LDS.
 enum Epi { kHidden, kQkv, kGate, kOut };
 
 struct Prod {
     const uint16_t* a;      // bf16 [M][K] (without NORM)
     const float* h;         // fp32 [M][K] (NORM)
-    const float* ssin;      // [M][K / 16] sums of squares of h (NORM)
+    const float* ssin;      // [M][nss] sums of squares of h over equal parts of a row (NORM)
+    int32_t nss;            // a multiple of 4
     const uint16_t* gain;   // bf16 [K] (NORM)
     const uint16_t* w;      // bf16 [N][K]
     int32_t M, N, K;
     const float* resid;     // kHidden: fp32 [M][N] added to the product, or null
     float* out;             // kHidden, kQkv: fp32 [M][N]
-    float* ssout;           // kHidden: [M][N / 16]
+    float* ssout;           // kHidden: [M][N / COLS]
     const uint16_t* resid16;// kOut: bf16 [M][N]
     uint16_t* out16;        // kGate: bf16 [M][N / 2]; kOut: bf16 [M][N]
 };
@@ -118,15 +119,16 @@ struct ProdUnit {
     u32x2 g;
 };
 
-template <int TM, int TN, int KW, int Q, int EPI, bool NORM>
+template <int TM, int TN, int KW, int Q, int EPI, bool NORM, int COLS = 16>
 __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
+    constexpr int WI = COLS / 8;  // eights of weight rows loaded per column tile
     constexpr int F = TM * TN, FPW = (F + KW - 1) / KW;
     constexpr int kBlk = 128;  // 16-byte slots per block of 16 rows x 64 channels
     __shared__ u32x4 stage[KW][(TM + TN) * kBlk];
     static_assert(F * kW <= (TM + TN) * kBlk, "a wavefront's sums fit in its staging slice");
     const uint32_t lane = threadIdx.x & (kW - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kW));
-    const int n0 = (int)blockIdx.x * (16 * TN), m0 = (int)blockIdx.y * (16 * TM);
+    const int n0 = (int)blockIdx.x * (COLS * TN), m0 = (int)blockIdx.y * (16 * TM);
     const uint32_t lr = lane & 15u, lq = lane >> 4;
     u32x4* const mine = stage[w];
     const int units = p.K >> 6;
@@ -139,8 +141,8 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
 #pragma unroll
     for (int t = 0; t < TN; ++t)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            wo[t][i] = (uint32_t)(n0 + 16 * t + 8 * i + (int)(lane >> 3)) * (uint32_t)p.K + kb + 8u * (lane & 7u);
+        for (int i = 0; i < WI; ++i)
+            wo[t][i] = (uint32_t)(n0 + COLS * t + 8 * i + (int)(lane >> 3)) * (uint32_t)p.K + kb + 8u * (lane & 7u);
 #pragma unroll
     for (int r = 0; r < TM; ++r) {
         if constexpr (NORM) {
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) b.w[t][i] = *reinterpret_cast<const u32x4*>(p.w + (wo[t][i] + k));
+            for (int i = 0; i < WI; ++i) b.w[t][i] = *reinterpret_cast<const u32x4*>(p.w + (wo[t][i] + k));
 #pragma unroll
         for (int r = 0; r < TM; ++r) {
             if constexpr (NORM) {
@@ -182,10 +184,10 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
     uint2 rs16[FPW];
 #pragma unroll
     for (int i = 0; i < FPW; ++i) {
-        const int f = w + i * KW, row = m0 + 16 * (f / TN) + (int)lr, col = n0 + 16 * (f % TN) + 4 * (int)lq;
+        const int f = w + i * KW, row = m0 + 16 * (f / TN) + (int)lr, col = n0 + COLS * (f % TN) + 4 * (int)lq;
         rs[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         rs16[i] = make_uint2(0u, 0u);
-        if (f < F && row < p.M) {
+        if (f < F && row < p.M && 4 * (int)lq < COLS) {
             if (EPI == kHidden && p.resid) rs[i] = *reinterpret_cast<const f32x4*>(p.resid + (size_t)row * p.N + col);
             if (EPI == kOut) rs16[i] = *reinterpret_cast<const uint2*>(p.resid16 + (size_t)row * p.N + col);
         }
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
     if constexpr (NORM) {
         // lane l sums every fourth group of four of row l / 4's sums of
         // squares, then the row's four lanes add theirs
-        const int nq = p.K >> 6;
+        const int nq = p.nss >> 2;
 #pragma unroll
         for (int r = 0; r < TM; ++r) {
             const f32x4* q = reinterpret_cast<const f32x4*>(p.ssin) + (size_t)arow(m0 + 16 * r + (int)(lane >> 2)) * nq;
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < WI; ++i)
                 mine[t * kBlk + slot_of(8u * i + r8, c >> 2, c & 3u)] = b.w[t][i];
 #pragma unroll
         for (int r = 0; r < TM; ++r) {
@@ -227,6 +229,7 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
                 const float g2 = __uint_as_float(b.g.y << 16), g3 = __uint_as_float(b.g.y & 0xFFFF0000u);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
+                    if (m0 + 16 * r + 4 * i >= p.M) continue;
                     const f32x4 h = b.h[r][i];
                     const float iv = inv[r][i];
                     const u32x2 o = {pack2(h[0] * iv * g0, h[1] * iv * g1), pack2(h[2] * iv * g2, h[3] * iv * g3)};
@@ -236,7 +239,7 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
             } else {
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    mine[(TN + r) * kBlk + slot_of(8u * i + r8, c >> 2, c & 3u)] = b.a[r][i];
+                    if (m0 + 16 * r + 8 * i < p.M) mine[(TN + r) * kBlk + slot_of(8u * i + r8, c >> 2, c & 3u)] = b.a[r][i];
             }
         }
     };
@@ -288,16 +291,16 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
         f32x4 v = reinterpret_cast<const f32x4*>(stage[0])[f * kW + lane];
 #pragma unroll
         for (int x = 1; x < KW; ++x) v = v + reinterpret_cast<const f32x4*>(stage[x])[f * kW + lane];
-        const int row = m0 + 16 * (f / TN) + (int)lr, col = n0 + 16 * (f % TN) + 4 * (int)lq;
-        const bool in = row < p.M;
+        const int row = m0 + 16 * (f / TN) + (int)lr, col = n0 + COLS * (f % TN) + 4 * (int)lq;
+        const bool in = row < p.M && 4 * (int)lq < COLS;
         if constexpr (EPI == kHidden) {
             v = rs[i] + v;
             float q = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
             q = q + __shfl_xor(q, 16);
-            q = q + __shfl_xor(q, 32);
+            if constexpr (COLS == 16) q = q + __shfl_xor(q, 32);
             if (in) {
                 *reinterpret_cast<f32x4*>(p.out + (size_t)row * p.N + col) = v;
-                if (lq == 0) p.ssout[(size_t)row * (p.N >> 4) + (col >> 4)] = q;
+                if (lq == 0) p.ssout[(size_t)row * (p.N / COLS) + col / COLS] = q;
             }
         } else if constexpr (EPI == kQkv) {
             if (in) *reinterpret_cast<f32x4*>(p.out + (size_t)row * p.N + col) = v;
@@ -575,7 +578,7 @@ PWork pwork(const rac_predictor_config* c, int B) {
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { const uint64_t at = o; o = up256(o + bytes); return at; };
     const uint64_t S = c->ffn % 512 == 0 && c->ffn > c->hidden ? f / 512 : (uint64_t)c->hidden / 512;
-    W.ss = take(S * B * m * 4);  // [B][m / 16] used
+    W.ss = take(S * B * m * 4);  // [B][m / 8] used at most
     W.h0 = take((uint64_t)B * m * 4);
     W.h1 = take((uint64_t)B * m * 4);
     W.h2 = take((uint64_t)B * m * 4);
@@ -587,12 +590,12 @@ PWork pwork(const rac_predictor_config* c, int B) {
     return W;
 }
 
-template <int TM, int TN, int KW, int Q, int EPI, bool NORM>
+template <int TM, int TN, int KW, int Q, int EPI, bool NORM, int COLS = 16>
 rac_status prod_launch(const Prod& p, hipStream_t st) {
     Prod a = p;
     void* args[] = {&a};
-    const dim3 grid((unsigned)(p.N / (16 * TN)), (unsigned)((p.M + 16 * TM - 1) / (16 * TM)), 1u);
-    return hipLaunchKernel(reinterpret_cast<const void*>(pred_prod<TM, TN, KW, Q, EPI, NORM>), grid, dim3(kW * KW),
+    const dim3 grid((unsigned)(p.N / (COLS * TN)), (unsigned)((p.M + 16 * TM - 1) / (16 * TM)), 1u);
+    return hipLaunchKernel(reinterpret_cast<const void*>(pred_prod<TM, TN, KW, Q, EPI, NORM, COLS>), grid, dim3(kW * KW),
                            args, 0, st) == hipSuccess
                ? RAC_OK
                : RAC_ERR_HIP;
@@ -611,11 +614,20 @@ int64_t tiles(const Prod& p, int tm, int tn) {
     return (int64_t)((p.M + 16 * tm - 1) / (16 * tm)) * (p.N / (16 * tn));
 }
 
-// Products onto the model width (few columns, long K).
-rac_status prod_hidden(const Prod& p, hipStream_t st) {
+// Products onto the model width (few columns, long K).  Up to 128 of the
+// smallest tiles leave half the chip idle: then eight columns a workgroup
+// (half of the matrix core's tile unused) on twice the workgroups.  us, 16
+// columns and 8: 1 x 512 of K = 4096: 4.6, 4.0; 64 x 512 of 4096 (128 tiles):
+// 5.3, 4.9; 128 x 512 of 4096 (256 tiles): 5.5, 7.1.
+rac_status prod_hidden(Prod& p, hipStream_t st) {
+    p.nss = p.N / 16;
+    if (tiles(p, 1, 1) <= 128) {
+        p.nss = p.N / 8;
+        return prod_launch<1, 1, 8, 2, kHidden, false, 8>(p, st);
+    }
     if (p.M > 16 && tiles(p, 2, 2) >= kFill) return prod_launch<2, 2, 8, 2, kHidden, false>(p, st);
     if (tiles(p, 1, 2) >= kFill) return prod_launch<1, 2, 8, 2, kHidden, false>(p, st);
-    return prod_launch<1, 1, 8, 4, kHidden, false>(p, st);
+    return prod_launch<1, 1, 8, 2, kHidden, false>(p, st);
 }
 
 // Products from the normalized model width (many columns, short K).
@@ -695,7 +707,7 @@ rac_status rac_predictor_step(const rac_predictor_config* cfg, const void* weigh
     const uint8_t* wb = static_cast<const uint8_t*>(weights);
     auto wt = [&](uint64_t off) { return reinterpret_cast<const uint16_t*>(wb + off); };
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    float* ss = reinterpret_cast<float*>(ws + Wb.ss);  // sums of squares of the residual stream, [B][m / 16]
+    float* ss = reinterpret_cast<float*>(ws + Wb.ss);  // sums of squares of the residual stream, [B][m / 16 or m / 8]
     float* h0 = reinterpret_cast<float*>(ws + Wb.h0);
     float* h1 = reinterpret_cast<float*>(ws + Wb.h1);
     float* h2 = reinterpret_cast<float*>(ws + Wb.h2);
