@@ -200,14 +200,22 @@ def _dev(t, what: str, elem_bytes, count: int):
     what it can)."""
     if t is None or isinstance(t, int):
         return t
+    try:
+        if t.is_cuda and t.is_contiguous() and t.element_size() == elem_bytes and t.numel() >= count:
+            return t.data_ptr()
+    except AttributeError:
+        pass
+    _refuse(t, what, elem_bytes, count)
+
+
+def _refuse(t, what: str, elem_bytes, count: int):
+    """Raises for an argument that _dev does not take."""
     if not (getattr(t, "is_cuda", False) and t.is_contiguous()):
         raise ValueError(f"{what}: expected a contiguous GPU tensor")
     es = t.element_size()
     if es != elem_bytes:
         raise ValueError(f"{what}: expected {elem_bytes}-byte elements, got {es}")
-    if t.numel() < count:
-        raise ValueError(f"{what}: holds {t.numel()} elements, needs {count}")
-    return t.data_ptr()
+    raise ValueError(f"{what}: holds {t.numel()} elements, needs {count}")
 
 
 def _xhat_bytes(cfg) -> int:
@@ -222,10 +230,22 @@ def _nbytes(t) -> int:
     return t.numel() * t.element_size()
 
 
+_torch = None
+
+
 def _stream(stream):
+    """The HIP stream of a call: the given one, or torch's current stream.  The
+    small calls are bound by the host: building the Stream object of
+    torch.cuda.current_stream() took 2.7 us of the 8.0 us of an encode call, so
+    its raw handle is read directly once the device is initialized."""
+    global _torch
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _torch is None:
+            import torch
+            _torch = torch
+        if _torch.cuda.is_initialized():
+            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        return _torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
