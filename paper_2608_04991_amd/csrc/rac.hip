@@ -47,10 +47,17 @@ constexpr int kMaxGatherRows = 64; // rows per workgroup with a gathered referen
 constexpr int kStridedRowsMax = 6; // beyond this many rows per resident workgroup: one workgroup per row
 constexpr uint32_t kMaxDispatchItems = 0xFFFFFFFFu;  // work-items one dispatch holds (per dimension)
 constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: adding it rounds to an integer (RNE)
-// Quotients t' = E * (1/s) within this distance of a half-integer are
-// recomputed with the correctly rounded division E / s.  |t' - E/s| is below
-// 2 ulp(128) = 2^-16 for |t'| <= 128, so the fast rounding is exact elsewhere.
-constexpr float kNearHalf = 0.5f - 0x1p-14f;
+// The product E * r, r = v_rcp_f32(s), is rounded to an integer; products whose
+// distance from that integer exceeds this (within (q + 1) 2^-22 of a tie) are
+// decided by the correctly rounded division E / s instead.  r is within an ulp
+// of 1/s (2^-23 relative; over every fp16 value of s the device's worst is 0.62
+// of that) and fl(E/s) within half an ulp of E/s, so the exact
+// product and fl(E/s) differ by less than 1.5 * 2^-23 |t| < 0.75 (q + 1) 2^-22
+// (|t| <= q + 1/2), and the fast rounding is exact elsewhere.  A fixed
+// 2^-14 sent 6% of the 512-channel chunks through the eight divisions of the
+// exact path at 4 bits; this sends 0.2%.
+template <int BITS>
+constexpr float kNearHalf = 0.5f - (float)(1 << (BITS - 1)) * 0x1p-22f;
 
 struct alignas(8) Args {
     // hot-path fields
@@ -240,6 +247,40 @@ __device__ __forceinline__ uint32_t step_roundup(float step) {
     for (int i = 0; i < 3; ++i)
         if (h > 1u && f16_value(h - 1u) >= step) --h;
     return h;
+}
+
+// Codes of a lane's 8 residuals ed at scale pattern sh (a6): qf[j] =
+// clamp(rint_even(fl(ed[j] / s)), +-Q) and mg[j] = qf[j] + 1.5 * 2^23, whose low
+// bits are the two's-complement code.  One fused multiply-add forms and rounds
+// the product, a second its distance from the integer.  |ed| <= s q unless a
+// scale saturated or the steps are calibrated ones (`clip`): then the residuals
+// are clamped to +-s q (exact), whose quotient is +-q.
+template <int BITS>
+__device__ __forceinline__ void quantize8(float* ed, uint32_t sh, float s, bool clip, float* mg, float* qf) {
+    constexpr float q = (float)((1 << (BITS - 1)) - 1);
+    const float inv = sh ? __builtin_amdgcn_rcpf(s) : 0.0f;
+    if (__builtin_amdgcn_ballot_w64(clip | (sh == 0x7C00u))) {
+        const float top = s * q;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ed[j] = __builtin_amdgcn_fmed3f(ed[j], -top, top);
+    }
+    float dist = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        mg[j] = __builtin_fmaf(ed[j], inv, kMagic);
+        qf[j] = mg[j] - kMagic;
+        dist = __builtin_fmaxf(dist, __builtin_fabsf(__builtin_fmaf(ed[j], inv, -qf[j])));
+    }
+    if (dist > kNearHalf<BITS>) {  // some quotient is near a tie: use the exact one
+        float inv2 = inv;
+        asm volatile("" : "+v"(inv2));  // recomputed here rather than kept live
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool near = __builtin_fabsf(__builtin_fmaf(ed[j], inv2, -qf[j])) > kNearHalf<BITS>;
+            mg[j] = near ? ed[j] / s + kMagic : mg[j];
+            qf[j] = mg[j] - kMagic;
+        }
+    }
 }
 
 // Closed-form least squares of one group from its centred moments:
@@ -1219,27 +1260,10 @@ void rac_encode_kernel(Args A) {
             bstore16(rsrc(A.scale, (uint64_t)row * ngq, ngq * 2u), first_q ? (uint32_t)grp_q * 2u : kOut, sh);
         }
         const float s = f16_wire(sh);
-        const float inv = sh ? __builtin_amdgcn_rcpf(s) : 0.0f;
 
         // a6-a8: quantize (round half to even), pack, reconstruct
-        float tc[8], mg[8], qf[8];
-        float dist = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            tc[j] = __builtin_amdgcn_fmed3f(ed[j] * inv, -q, q);
-            mg[j] = tc[j] + kMagic;
-            qf[j] = mg[j] - kMagic;
-            dist = __builtin_fmaxf(dist, __builtin_fabsf(tc[j] - qf[j]));
-        }
-        if (dist > kNearHalf) {  // some quotient is near a tie: use the exact one
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (__builtin_fabsf(tc[j] - qf[j]) > kNearHalf) {
-                    tc[j] = __builtin_amdgcn_fmed3f(ed[j] / s, -q, q);
-                    mg[j] = tc[j] + kMagic;
-                    qf[j] = mg[j] - kMagic;
-                }
-        }
+        float mg[8], qf[8];
+        quantize8<BITS>(ed, sh, s, A.fixed != 0, mg, qf);
         Packed<BITS> pk{};
         float H[8];
 #pragma unroll
@@ -1868,30 +1892,8 @@ void rac_encode_rows_kernel(Args A) {
             const uint32_t sh = m == 0.0f ? 0u : scale_roundup(m, q, inv_q);
             bstore16(rsc, first_q ? (c0 >> A.lg_q) * 2u : kOut, sh);
             const float s = f16_wire(sh);
-            const float inv = sh ? __builtin_amdgcn_rcpf(s) : 0.0f;
-            // |E^d| <= s q, so E^d * (1/s) stays below q + 1/2 unless the
-            // scale saturated; that case and quotients near a tie take the
-            // clamped, correctly rounded path
             float mg[8], qf[8];
-            float dist = 0.0f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float t = ed[j] * inv;
-                mg[j] = t + kMagic;
-                qf[j] = mg[j] - kMagic;
-                dist = __builtin_fmaxf(dist, __builtin_fabsf(t - qf[j]));
-            }
-            if ((dist > kNearHalf) | (sh == 0x7C00u)) {
-                float inv2 = inv;
-                asm volatile("" : "+v"(inv2));  // recomputed here rather than kept live
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float t0 = ed[j] * inv2;
-                    const float t = __builtin_fabsf(t0 - qf[j]) > kNearHalf ? ed[j] / s : t0;
-                    mg[j] = __builtin_amdgcn_fmed3f(t, -q, q) + kMagic;
-                    qf[j] = mg[j] - kMagic;
-                }
-            }
+            quantize8<BITS>(ed, sh, s, false, mg, qf);
             float H[8];
             {
                 float r[8];
