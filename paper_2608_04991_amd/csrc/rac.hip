@@ -44,7 +44,12 @@ constexpr int kChunk = 512;       // channels per wavefront (8 per lane)
 constexpr int kMaxWaves = 16;     // rows up to 8192 channels
 constexpr int kCandCap = 64;      // outlier candidates ranked by one wavefront (twice that for k > 48)
 constexpr int kMaxGatherRows = 64; // rows per workgroup with a gathered reference
-constexpr int kStridedRowsMax = 6; // beyond this many rows per resident workgroup: one workgroup per row
+// Launch shape (see launch): beyond this many rows per resident workgroup, one
+// workgroup per row
+constexpr int kStridedRowsMax = 6;
+constexpr int kWideStridedRowsMax = 4;
+constexpr int kManyRows = 8192;
+constexpr size_t kSevenPerCu = 2560;  // LDS bytes that keep an eighth workgroup off a compute unit
 constexpr uint32_t kMaxDispatchItems = 0xFFFFFFFFu;  // work-items one dispatch holds (per dimension)
 constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: adding it rounds to an integer (RNE)
 // The product E * r, r = v_rcp_f32(s), is rounded to an integer; products whose
@@ -624,7 +629,7 @@ __device__ __forceinline__ void store_xhat(Rsrc rx, bool bf16, uint32_t c0, cons
 // by the 64 lanes covers 1 KiB of consecutive float4s, and the 8-float4 gap
 // puts the two planes in different banks for the transposed read below.
 constexpr int kPlane = kWave + 8;
-constexpr int kSlice = 2 * kPlane;  // float4 per slice
+constexpr int kSlice = kPlane + kWave;  // float4 per slice
 
 __device__ __forceinline__ void put8(float4* st, uint32_t lane, const float* v) {
     st[lane] = make_float4(v[0], v[1], v[2], v[3]);
@@ -1302,44 +1307,61 @@ constexpr int kKeyChBits = 13;               // channel bits of the exact search
 constexpr int kTop1 = 16;  // largest k whose first threshold comes from one maximum per lane
 constexpr int kTop2 = 48;  // largest k whose first threshold takes two per wavefront lane (beyond: four)
 
-// The third and fourth largest |E| of each (wavefront, lane), kept only with
-// the larger candidate list.
-template <int NW, bool MORE>
-struct LaneMaxMore {
+// The second largest |E| of each (wavefront, lane) (k > kTop1), and the third
+// and fourth, kept only with the larger candidate list.
+template <int NW, int MAXES>
+struct LaneMaxMore {};
+template <int NW>
+struct LaneMaxMore<NW, 2> {
+    uint32_t smax2[NW][kWave];
+};
+template <int NW>
+struct LaneMaxMore<NW, 4> {
+    uint32_t smax2[NW][kWave];
     uint32_t smax3[NW][kWave];
     uint32_t smax4[NW][kWave];
 };
-template <int NW>
-struct LaneMaxMore<NW, false> {};
+// The coefficient pair of each candidate's group (not kept with one workgroup
+// per row, whose candidates carry R~).
+template <int CAP, bool KEEP>
+struct CandCoef {
+    uint32_t ccf[CAP];
+};
+template <int CAP>
+struct CandCoef<CAP, false> {};
 
-template <int NW, int CAP = kCandCap>
-struct alignas(16) GroupShared : LaneMaxMore<NW, (CAP > kCandCap)> {
+// (With one workgroup per row, k <= kTop2 and two chunks a wavefront the
+// kernel's LDS is at most 20480 bytes, an eighth of a compute unit's: eight
+// workgroups a unit, 2048 on the chip.)
+template <int NW, int CAP, int MAXES, bool COEF>
+struct alignas(16) GroupShared : LaneMaxMore<NW, MAXES>, CandCoef<CAP, COEF> {
     static constexpr int cap = CAP;  // candidate list capacity
     // (ckey and cval, contiguous, also hold the exact search's three
     // 64-bin histograms while the list is dropped)
     uint64_t ckey[CAP];  // candidates: |E| bits << 32 | (0xFFFF - channel)
     uint32_t cval[CAP];  // their E bits
-    uint32_t crw[CAP];   // their ref word (the bf16 pair holding the channel)
-    uint32_t ccf[CAP];   // their group's coefficient pair
+    uint32_t crw[CAP];   // their ref word (the bf16 pair holding the channel), or R~ itself (ONE)
     uint32_t smax[NW][kWave]; // lane maxima of |E| of each wavefront
-    uint32_t smax2[NW][kWave];// the lanes' second largest |E| (k > kTop1)
-    uint32_t thr;             // that threshold, from wavefront 0
-    uint32_t cnt[2];          // candidate count (LDS atomic), by row parity
-    uint32_t xn[2];           // count of the rebuilt list (exact search), by row parity
 };
-static_assert(offsetof(GroupShared<4>, cval) == sizeof(uint64_t) * kCandCap &&
-                  sizeof(uint64_t) * kCandCap + sizeof(uint32_t) * kCandCap >= 3 * kWave * sizeof(uint32_t),
+// A row's counters, kept in the gap between the two planes of the first slice.
+struct RowCounters {
+    uint32_t thr;     // the threshold, from wavefront 0 (k > kTop1)
+    uint32_t cnt[2];  // candidate count (LDS atomic), by row parity
+    uint32_t xn[2];   // count of the rebuilt list (exact search), by row parity
+};
+static_assert(sizeof(RowCounters) <= sizeof(float4) * (kPlane - kWave), "the counters fit in a slice's gap");
+static_assert(sizeof(uint64_t) * kCandCap + sizeof(uint32_t) * kCandCap >= 3 * kWave * sizeof(uint32_t),
               "the histograms of the exact search fit in ckey and cval");
 
 // Append this lane's elements of one chunk whose |E| pattern is >= lo (and,
 // with use_key, whose key is >= kmin) to the shared candidate list, with
 // what R~ is formed from (the loaded ref word and the coefficient pair
-// cfv); one LDS atomic per wavefront reserves the slots, entries beyond the
+// cfv) or, with ONE, R~ itself; one LDS atomic per wavefront reserves the slots, entries beyond the
 // list's capacity are counted but not stored.
-template <class G>
+template <bool ONE, class G>
 __device__ __forceinline__ void append_shared(G& S, uint32_t* counter,
-                                              const float* e, const uint4& rpk, uint32_t cfv, bool act, uint32_t c0,
-                                              uint32_t lo, bool use_key, uint64_t kmin, uint32_t lane) {
+                                              const float* e, const uint4& rpk, uint32_t cfv, const float* rt, bool act,
+                                              uint32_t c0, uint32_t lo, bool use_key, uint64_t kmin, uint32_t lane) {
     bool p[8];
     uint32_t n = 0;
 #pragma unroll
@@ -1361,8 +1383,8 @@ __device__ __forceinline__ void append_shared(G& S, uint32_t* counter,
             if (p[j] & (pos < (uint32_t)G::cap)) {
                 S.ckey[pos] = cand_key(__float_as_uint(e[j]), c0 + j);
                 S.cval[pos] = __float_as_uint(e[j]);
-                S.crw[pos] = rw[j >> 1];
-                S.ccf[pos] = cfv;
+                S.crw[pos] = ONE ? __float_as_uint(rt[j]) : rw[j >> 1];
+                if constexpr (!ONE) S.ccf[pos] = cfv;
             }
             base += (uint32_t)__builtin_popcountll(m);
         }
@@ -1374,9 +1396,9 @@ __device__ __forceinline__ void append_shared(G& S, uint32_t* counter,
 // the float order of |E| is the order of its bit patterns).  A lane's mask
 // bit comes from its compare ANDed with the wavefront's active-lane mask
 // (ballot of act), so each element costs one vector compare.
-template <class G>
+template <bool ONE, class G>
 __device__ __forceinline__ void append_bound(G& S, uint32_t* counter, const float* e, const uint4& rpk, uint32_t cfv,
-                                             bool act, uint32_t c0, float Lf, uint32_t lane) {
+                                             const float* rt, bool act, uint32_t c0, float Lf, uint32_t lane) {
     const uint64_t actm = ballot(act);
     uint32_t n = 0;
 #pragma unroll
@@ -1394,8 +1416,8 @@ __device__ __forceinline__ void append_bound(G& S, uint32_t* counter, const floa
             if (act & (__builtin_fabsf(e[j]) >= Lf) & (pos < (uint32_t)G::cap)) {
                 S.ckey[pos] = cand_key(__float_as_uint(e[j]), c0 + j);
                 S.cval[pos] = __float_as_uint(e[j]);
-                S.crw[pos] = rw[j >> 1];
-                S.ccf[pos] = cfv;
+                S.crw[pos] = ONE ? __float_as_uint(rt[j]) : rw[j >> 1];
+                if constexpr (!ONE) S.ccf[pos] = cfv;
             }
             base += (uint32_t)__builtin_popcountll(m);
         }
@@ -1446,15 +1468,20 @@ __device__ __forceinline__ void opaque_n(uint4 (&r)[N]) {
 // BIG: the first threshold from the four largest |E| of each (wavefront,
 // lane) and a candidate list of 2 * kCandCap entries, ranked two per lane
 // (for k > kTop2, whose rows would overflow the smaller list almost always).
-template <int BITS, int GA, int GQ, int NW, int CPW, bool GIVEN, bool TWO, bool BIG = false>
-__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(CPW == 2 ? (BIG ? 6 : 7) : 4)))
+// ONE: one workgroup per row: no next row to prefetch, so the registers of the
+// prefetched x and of the packed ref hold R~ instead, which phase C and the
+// outliers would otherwise form again from ref (a twentieth of the row's
+// vector instructions).
+template <int BITS, int GA, int GQ, int NW, int CPW, bool GIVEN, bool TWO, bool BIG = false, bool ONE = false>
+__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(CPW == 2 ? (BIG ? 6 : ONE ? 8 : 7) : 4)))
 void rac_encode_rows_kernel(Args A) {
     // (a row's lists are read before the next row's first barrier and
     // written after it; only the count is reset early, so it alternates)
-    __shared__ GroupShared<NW, BIG ? 2 * kCandCap : kCandCap> S;
+    __shared__ GroupShared<NW, BIG ? 2 * kCandCap : kCandCap, BIG ? 4 : TWO ? 2 : 1, !ONE> S;
     // E of each wavefront's chunks (one slice per chunk), later the staging
     // of the chunk's reconstruction
     __shared__ float4 EL[NW][CPW][kSlice];
+    RowCounters& RC = *reinterpret_cast<RowCounters*>(&EL[0][0][kWave]);
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const int w = (int)uniform(threadIdx.x / kWave);
     const int d = A.d, k = A.k;
@@ -1470,13 +1497,14 @@ void rac_encode_rows_kernel(Args A) {
     // first channel of the wavefront's i-th chunk: chunks are dealt round the
     // wavefronts, so a row of fewer than NW * CPW chunks stays balanced
     auto chunk_at = [&](int i) { return (w + i * NW) * kChunk; };
-    const int32_t rix = load_ref_rows_v(A, lane);  // store rows of the gathered reference
+    const int32_t rix = ONE ? 0 : load_ref_rows_v(A, lane);  // store rows of the gathered reference
     const int32_t fix = first_ref_index(A);
     if (w == 0 && lane < 2u) {
-        S.cnt[lane] = 0u;
-        S.xn[lane] = 0u;
+        RC.cnt[lane] = 0u;
+        RC.xn[lane] = 0u;
     }
-    __syncthreads();
+    // (with one row the first barrier of the row orders this)
+    if constexpr (!ONE) __syncthreads();
 
     // x and ref of the block's first row; later rows are prefetched into
     // the same registers as they fall free (x after the fit, each ref chunk
@@ -1499,11 +1527,11 @@ void rac_encode_rows_kernel(Args A) {
     // analysis then keeps the memory operations in order across the loop and
     // the fit waits for the prefetched loads, not for the previous row's
     // stores issued after them.
-    bstore32(rsrc(A.coef, 0, 0u), kOut, 0u);
+    if constexpr (!ONE) bstore32(rsrc(A.coef, 0, 0u), kOut, 0u);
 
     uint32_t n = 0;
     for (uint32_t row = blockIdx.x; row < A.tokens; row += gridDim.x, ++n) {
-        uint32_t* const cnt = &S.cnt[n & 1];
+        uint32_t* const cnt = &RC.cnt[n & 1];
         // lane * 8, opaque inside the loop: otherwise every per-channel
         // constant of the lane's channels is hoisted out of the row loop
         // (the lane id is recomputed, not kept live across the loop)
@@ -1520,6 +1548,7 @@ void rac_encode_rows_kernel(Args A) {
         const uint64_t on = (uint64_t)nrow * (uint64_t)d;
         const Rsrc nx = rsrc(A.x, on, more ? row_bytes : 0u), nr = ref_row(A, nrow, more, ref_index_v(A, rix, n + 1u));
         uint32_t cf[CPW];
+        float rt[ONE ? CPW : 1][8];  // ONE: R~ of the lane's channels
 #pragma unroll
         for (int i = 0; i < CPW; ++i) cf[i] = 0u;
 
@@ -1559,7 +1588,9 @@ void rac_encode_rows_kernel(Args A) {
             float e[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {  // E = 0 past the row
-                e[j] = x[j] - __builtin_fmaf(a, r[j], b0);
+                const float t = __builtin_fmaf(a, r[j], b0);
+                e[j] = x[j] - t;
+                if constexpr (ONE) rt[i][j] = t;
                 lmc[i] = __builtin_fmaxf(lmc[i], __builtin_fabsf(e[j]));
             }
             put8(EL[w][i], lane, e);
@@ -1568,8 +1599,10 @@ void rac_encode_rows_kernel(Args A) {
 #pragma unroll
         for (int i = 1; i < CPW; ++i) lmx = __builtin_fmaxf(lmx, lmc[i]);
 
+        if constexpr (!ONE) {
 #pragma unroll
-        for (int i = 0; i < CPW; ++i) xl[i] = bload128(nx, ((uint32_t)(chunk_at(i)) + l8) * 2u);
+            for (int i = 0; i < CPW; ++i) xl[i] = bload128(nx, ((uint32_t)(chunk_at(i)) + l8) * 2u);
+        }
 
         // a4: the k largest |E| of the row (ties to the lower channel).
         // Threshold L: the k-th largest of the 64 maxima of |E| over lane l
@@ -1625,9 +1658,9 @@ void rac_encode_rows_kernel(Args A) {
         __syncthreads();
         // the other buffer was last read by the previous row, which every
         // wavefront has left: reset its candidate count for the next row
-        if (w == 0 && lane == 0u) {
-            S.cnt[(n + 1) & 1] = 0u;
-            S.xn[(n + 1) & 1] = 0u;
+        if (!ONE && w == 0 && lane == 0u) {
+            RC.cnt[(n + 1) & 1] = 0u;
+            RC.xn[(n + 1) & 1] = 0u;
         }
         uint32_t v = S.smax[0][lane];
 #pragma unroll
@@ -1678,12 +1711,12 @@ void rac_encode_rows_kernel(Args A) {
                              (uint32_t)__builtin_popcountll(ballot(a4 >= cnd));
                     if (c >= (uint32_t)k) L = cnd;
                 }
-                if (lane == 0u) S.thr = L;
+                if (lane == 0u) RC.thr = L;
             }
             __syncthreads();
-            L = uniform(S.thr);
+            L = uniform(RC.thr);
         }
-        opaque_n(rp);
+        if constexpr (!ONE) opaque_n(rp);
         const float Lf = __uint_as_float(L);
 #pragma unroll
         for (int i = 0; i < CPW; ++i) {
@@ -1692,7 +1725,7 @@ void rac_encode_rows_kernel(Args A) {
             const uint32_t c0 = (uint32_t)(chunk_at(i)) + l8;
             float e[8];
             get8(EL[w][i], lane, e);
-            append_bound(S, cnt, e, rp[i], cf[i], c0 < (uint32_t)d, c0, Lf, lane);
+            append_bound<ONE>(S, cnt, e, rp[i], cf[i], rt[ONE ? i : 0], c0 < (uint32_t)d, c0, Lf, lane);
         }
         __syncthreads();
         // k-th largest of the first Cn listed keys (Cn <= S.cap; lane i
@@ -1795,14 +1828,14 @@ void rac_encode_rows_kernel(Args A) {
             const uint64_t kl = (prefix << shift) >> 5;
             const uint32_t pm = (uint32_t)(kl >> kKeyChBits), cm = (uint32_t)(kl & kChMax);
             const uint64_t kmin = ((uint64_t)pm << 32) | (uint64_t)(0xFFFFu - kChMax + cm);
-            uint32_t* const xc = &S.xn[n & 1];
+            uint32_t* const xc = &RC.xn[n & 1];
             __syncthreads();  // (every wavefront has read the last histogram)
 #pragma unroll
             for (int i = 0; i < CPW; ++i) {
                 const uint32_t c0 = (uint32_t)(chunk_at(i)) + l8;
                 float e[8];
                 get8(EL[w][i], lane, e);
-                append_shared(S, xc, e, rp[i], cf[i], c0 < (uint32_t)d, c0, pm, true, kmin, lane);
+                append_shared<ONE>(S, xc, e, rp[i], cf[i], rt[ONE ? i : 0], c0 < (uint32_t)d, c0, pm, true, kmin, lane);
             }
             __syncthreads();
             C = uniform(*xc);  // k <= C <= S.cap
@@ -1821,9 +1854,13 @@ void rac_encode_rows_kernel(Args A) {
         float ohat = 0.0f;
         if (chosen) {
             oval = f16_rne(__uint_as_float(S.cval[lane]));
-            const uint32_t rw = S.crw[lane], cfc = S.ccf[lane];
-            const float r = (och & 1u) ? bf16_hi(rw) : bf16_lo(rw);
-            ohat = __builtin_fmaf(f16_wire(cfc & 0xFFFFu), r, f16_wire(cfc >> 16)) + f16_wire(oval);
+            const uint32_t rw = S.crw[lane];
+            float t = __uint_as_float(rw);
+            if constexpr (!ONE) {
+                const uint32_t cfc = S.ccf[lane];
+                t = __builtin_fmaf(f16_wire(cfc & 0xFFFFu), (och & 1u) ? bf16_hi(rw) : bf16_lo(rw), f16_wire(cfc >> 16));
+            }
+            ohat = t + f16_wire(oval);
         }
         bool chosen2 = false;
         uint32_t och2 = 0xFFFFFFFFu, oval2 = 0u;
@@ -1834,9 +1871,14 @@ void rac_encode_rows_kernel(Args A) {
                 const uint32_t i2 = lane + (uint32_t)kWave;
                 och2 = key_channel(key2);
                 oval2 = f16_rne(__uint_as_float(S.cval[i2]));
-                const uint32_t rw = S.crw[i2], cfc = S.ccf[i2];
-                const float r = (och2 & 1u) ? bf16_hi(rw) : bf16_lo(rw);
-                ohat2 = __builtin_fmaf(f16_wire(cfc & 0xFFFFu), r, f16_wire(cfc >> 16)) + f16_wire(oval2);
+                const uint32_t rw = S.crw[i2];
+                float t = __uint_as_float(rw);
+                if constexpr (!ONE) {
+                    const uint32_t cfc = S.ccf[i2];
+                    t = __builtin_fmaf(f16_wire(cfc & 0xFFFFu), (och2 & 1u) ? bf16_hi(rw) : bf16_lo(rw),
+                                       f16_wire(cfc >> 16));
+                }
+                ohat2 = t + f16_wire(oval2);
             }
         }
         if (w == 0) {
@@ -1873,7 +1915,7 @@ void rac_encode_rows_kernel(Args A) {
         wave_lds_sync();
 
         // a5-a8 per chunk: scale, quantize, pack, reconstruct
-        opaque_n(rp);
+        if constexpr (!ONE) opaque_n(rp);
         const Rsrc rsc = rsrc(A.scale, (uint64_t)row * ngq, ngq * 2u);
         const Rsrc rcd = rsrc(A.codes, (uint64_t)row * crb, crb);
         const Rsrc rxh = xhat_row(A, row);
@@ -1894,15 +1936,18 @@ void rac_encode_rows_kernel(Args A) {
             const float s = f16_wire(sh);
             float mg[8], qf[8];
             quantize8<BITS>(ed, sh, s, false, mg, qf);
-            float H[8];
-            {
+            float H[8];  // R~ + q*s (q*s exact)
+            if constexpr (ONE) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) H[j] = __builtin_fmaf(qf[j], s, rt[i][j]);
+            } else {
                 float r[8];
                 widen8(rp[i], r);
                 const float a = f16_wire(cf[i] & 0xFFFFu), b0 = f16_wire(cf[i] >> 16);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) H[j] = __builtin_fmaf(qf[j], s, __builtin_fmaf(a, r[j], b0));  // R~ + q*s (q*s exact)
+                for (int j = 0; j < 8; ++j) H[j] = __builtin_fmaf(qf[j], s, __builtin_fmaf(a, r[j], b0));
+                rp[i] = bload128(nr, c0 * 2u);
             }
-            rp[i] = bload128(nr, c0 * 2u);
             store_codes<BITS>(rcd, w + i * NW, lane, dword3, pack8<BITS>(mg));
             put8(st, lane, H);
             wave_lds_sync();
@@ -1912,6 +1957,7 @@ void rac_encode_rows_kernel(Args A) {
             wave_lds_sync();
             emit_xhat(rxh, A.xhat_bf16 != 0, chunk0, l8 >> 3, st);
         }
+        if constexpr (ONE) return;
     }
 }
 
@@ -2493,18 +2539,35 @@ KernelFn pick_encode(const Args& A, int bits) {
     return encode_for<-1, -1>(bits, om);
 }
 
+// The rows kernel in its two launch shapes: workgroups that take rows in
+// strides of the grid, and one workgroup per row (null with given pairs, whose
+// search for the row's segment the strided form overlaps with the row before:
+// 4096 x 4096 pooled 43.5 us strided, 47.0 with one workgroup per row).
+struct RowsKernels {
+    KernelFn strided, one;
+};
+
+template <int BITS, int GA, int GQ, int CPW, bool GIVEN, bool TWO, bool BIG>
+RowsKernels rows_pair() {
+    if constexpr (GIVEN)
+        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, true, TWO, BIG>, nullptr};
+    else
+        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG>,
+                rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG, true>};
+}
+
 template <int GA, int GQ, int CPW, bool GIVEN, bool TWO, bool BIG>
-KernelFn rows_for_bits(int bits) {
+RowsKernels rows_for_bits(int bits) {
     switch (bits) {
-        case 2: return rac_encode_rows_kernel<2, GA, GQ, kRowsWaves, CPW, GIVEN, TWO, BIG>;
-        case 3: return rac_encode_rows_kernel<3, GA, GQ, kRowsWaves, CPW, GIVEN, TWO, BIG>;
-        case 4: return rac_encode_rows_kernel<4, GA, GQ, kRowsWaves, CPW, GIVEN, TWO, BIG>;
-        default: return rac_encode_rows_kernel<8, GA, GQ, kRowsWaves, CPW, GIVEN, TWO, BIG>;
+        case 2: return rows_pair<2, GA, GQ, CPW, GIVEN, TWO, BIG>();
+        case 3: return rows_pair<3, GA, GQ, CPW, GIVEN, TWO, BIG>();
+        case 4: return rows_pair<4, GA, GQ, CPW, GIVEN, TWO, BIG>();
+        default: return rows_pair<8, GA, GQ, CPW, GIVEN, TWO, BIG>();
     }
 }
 
 template <int GA, int GQ, int CPW, bool GIVEN>
-KernelFn rows_for_cpw(int bits, int k) {
+RowsKernels rows_for_cpw(int bits, int k) {
     if constexpr (GIVEN) {
         return rows_for_bits<GA, GQ, CPW, true, false, false>(bits);
     } else {
@@ -2519,7 +2582,7 @@ KernelFn rows_for_cpw(int bits, int k) {
 // candidate list beyond (not with given pairs, which keep the one-value
 // bound and the smaller list: every bound and list size is exact).
 template <int GA, int GQ, bool GIVEN = false>
-KernelFn rows_for(int bits, int d, int k) {
+RowsKernels rows_for(int bits, int d, int k) {
     if (d <= kRowsWaves * 2 * kChunk) return rows_for_cpw<GA, GQ, 2, GIVEN>(bits, k);
     return rows_for_cpw<GA, GQ, 4, GIVEN>(bits, k);
 }
@@ -2531,7 +2594,7 @@ bool use_rows_kernel(const Args& A) {
     return outlier_mode(A) == 1 && !A.fixed && A.d <= kRowsMaxD && A.lg_cpg_a == 0 && A.lg_cpg_q == 0;
 }
 
-KernelFn pick_rows(const Args& A, int bits) {
+RowsKernels pick_rows(const Args& A, int bits) {
     // given pairs (pooled fit): the fixed 128 and 64 shapes and the generic one
     if (A.cf_given) {
         if (A.lane_lv_a == 4 && A.lane_lv_q == 4) return rows_for<4, 4, true>(bits, A.d, A.k);
@@ -2611,31 +2674,43 @@ rac_status device_cus(int* cus) {
     return resident(nullptr, 0, 0, cus, &unused);
 }
 
-// One workgroup per token row.  Large row counts use a grid of as many
-// workgroups as the device keeps resident (at most max_per_cu per compute
-// unit), each taking rows in strides (and prefetching its next row); small
-// counts, and counts that would give every resident workgroup more than
-// kStridedRowsMax rows, launch one workgroup per row.  The launch flags of the
-// configuration override that choice for more than 256 rows.  (Over many rows the
-// strided workgroups drift apart, so the rows in flight spread over the
-// tensors and the HBM writes lose locality; with one workgroup per row the
-// dispatcher hands rows out in order as workgroups finish, which keeps them
-// together.  Measured on a 65536 x 3584 tensor: 9% off the encode, 13% off
-// the decode; at four rows per workgroup the two are even.)
-rac_status launch(KernelFn fn, Args A, hipStream_t stream, int threads = 0, int max_per_cu = 0) {
+// Over many rows strided workgroups (each taking rows in strides of a grid of
+// as many workgroups as the device keeps resident, at most max_per_cu per
+// compute unit, with its next row prefetched) drift apart, so the rows in
+// flight spread over the tensors and the HBM writes lose locality; with one
+// workgroup per row the dispatcher hands rows out in order as workgroups
+// finish, which keeps them together.  Up to 256 rows every workgroup takes one
+// row; beyond that the shape is chosen by rows per resident workgroup, and the
+// launch flags of the configuration override the choice.
+//   - Kernels with one form only (`one` null): strided up to
+//     kStridedRowsMax.  At 65536 x 3584 one workgroup per row is 13% faster
+//     for the decode; at four rows per workgroup the two are even.
+//   - Per-token outliers (`one`: the form that holds no next row), up to
+//     4096 channels: always one workgroup per row.  k = 8, us, strided and one
+//     per row: 2048 x 4096 18.1 and 15.8, 4096 x 4096 31.0 and 30.4, 16384 x
+//     4096 110.8 and 103.6, 4096 x 2048 20.9 and 18.6.
+//   - Wider rows (four chunks a wavefront, half as many workgroups resident):
+//     strided up to kWideStridedRowsMax.  2048 x 8192 30.6 and 31.6, 4096 x
+//     8192 57.0 and 57.8, 6144 x 8192 83.3 and 81.2.
+//   - Over kManyRows rows of more than 2048 channels with k <= kTop1, seven
+//     workgroups a compute unit instead of eight, by LDS that is requested and
+//     not used: 65536 x 3584 339.8 against 350.6 us, 32768 x 4096 194.8
+//     against 197.5 (32768 x 2048, which stays at eight, 109.2 against 107.1).
+rac_status launch(KernelFn fn, Args A, hipStream_t stream, int threads = 0, int max_per_cu = 0,
+                  KernelFn one = nullptr) {
     const int64_t rows = A.tokens;
     // kernels launched with one wavefront per chunk stage through a
     // dynamically sized slice per wavefront
     const bool staged = threads == 0;
     if (staged) threads = A.nch * kWave;
-    const size_t lds = staged ? (size_t)A.nch * kSlice * sizeof(float4) : 0;
+    size_t lds = staged ? (size_t)A.nch * kSlice * sizeof(float4) : 0;
     int64_t blocks = rows <= 0 ? 1 : rows;
-    if (rows > 256) {
+    const int64_t strided_max = !one ? kStridedRowsMax : A.nch > 2 * kRowsWaves ? kWideStridedRowsMax : 0;
+    if (rows > 256 && A.launch_shape != 2 && (strided_max > 0 || A.launch_shape == 1)) {
         int cus = 0, per_cu = 0;
         if (resident(reinterpret_cast<const void*>(fn), threads, lds, &cus, &per_cu) != RAC_OK) return RAC_ERR_HIP;
         const int64_t fits = (int64_t)cus * (per_cu > 0 ? per_cu : 1);  // workgroups the device holds at once
-        const bool strided = A.launch_shape == 1 || (A.launch_shape == 0 && rows <= kStridedRowsMax * fits);
-        if (strided) {
+        if (A.launch_shape == 1 || rows <= strided_max * fits) {
             if (max_per_cu > 0 && per_cu > max_per_cu) per_cu = max_per_cu;
             int64_t resident = (int64_t)cus * (per_cu > 0 ? per_cu : 1);
             // a gathered reference: at most kMaxGatherRows rows per workgroup,
@@ -2646,12 +2721,16 @@ rac_status launch(KernelFn fn, Args A, hipStream_t stream, int threads = 0, int 
         }
     }
     // A dispatch holds fewer than 2^32 work-items per dimension: beyond that
-    // the workgroups stride over the rows (every kernel takes rows in strides
-    // of the grid).  A gathered reference allows at most kMaxGatherRows rows
-    // per workgroup.
+    // the workgroups stride over the rows (every kernel but `one` takes rows in
+    // strides of the grid).  A gathered reference allows at most kMaxGatherRows
+    // rows per workgroup.
     const int64_t max_blocks = (int64_t)(kMaxDispatchItems / (uint32_t)threads);
     if (blocks > max_blocks) blocks = max_blocks;
     if (A.ref_rows && blocks * kMaxGatherRows < rows) return RAC_ERR_UNSUPPORTED;
+    if (one && blocks == rows) {
+        fn = one;
+        if (rows > kManyRows && A.k <= kTop1 && A.nch > kRowsWaves && A.nch <= 2 * kRowsWaves) lds = kSevenPerCu;
+    }
     void* args[] = {&A};
     const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)blocks),
                                          dim3((unsigned)threads), args, lds, stream);
@@ -2810,7 +2889,10 @@ rac_status run_encode(const rac_config* cfg, const void* x, const void* ref, con
     A.xhat = xhat;
     A.write_header = 1;
     fill_header(A, cfg, ref == nullptr);
-    if (use_rows_kernel(A)) return launch(pick_rows(A, cfg->bits), A, stream, kRowsWaves * kWave);
+    if (use_rows_kernel(A)) {
+        const RowsKernels k = pick_rows(A, cfg->bits);
+        return launch(k.strided, A, stream, kRowsWaves * kWave, 0, k.one);
+    }
     return launch(pick_encode(A, cfg->bits), A, stream);
 }
 
@@ -2888,7 +2970,10 @@ rac_status rac_encode_pooled(const rac_config* cfg, const void* x, const void* r
     A.cf_given = 1;
     A.write_header = 1;
     fill_header(A, cfg, ref == nullptr, true);
-    if (use_rows_kernel(A)) return launch(pick_rows(A, cfg->bits), A, stream, kRowsWaves * kWave);
+    if (use_rows_kernel(A)) {
+        const RowsKernels k = pick_rows(A, cfg->bits);
+        return launch(k.strided, A, stream, kRowsWaves * kWave, 0, k.one);
+    }
     return launch(pick_encode(A, cfg->bits), A, stream);
 }
 

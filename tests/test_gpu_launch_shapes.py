@@ -169,3 +169,31 @@ def test_more_rows_than_one_dispatch_holds():
     assert torch.equal(wg, wm)
     del x, ix, wg, wm
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d,g,k,bits", [(520, 8, 1, 4), (2048, 128, 16, 2), (4096, 128, 17, 3), (4096, 64, 48, 8),
+                                        (4096, 128, 49, 4), (5120, 128, 16, 4), (8192, 64, 64, 3)])
+def test_one_row_and_strided_forms_on_ties_and_plain_rows(d, g, k, bits):
+    # the per-token kernel's two forms (one workgroup per row, which keeps R~;
+    # strided, which forms it again) on rows of equal |E| (the candidate list
+    # overflows and the exact search runs), rows with a zero residual and
+    # ordinary ones; at the edges of the threshold's variants (k = 16, 17, 48,
+    # 49), of two and four chunks a wavefront, and of a ragged last chunk
+    T = 300
+    rng = np.random.default_rng([d, k])
+    xb, rb, _ = wl.prefill_uplink(11, tokens=T, hidden=d) if d % 128 == 0 else \
+        wl.affine_pair(wl.AffineRecipe(T, d, 8), 11)
+    xb, rb = xb.copy(), rb.copy()
+    xb[0::3] = wl.f32_to_bf16_bits(rng.choice([-1.5, 1.5], size=xb[0::3].shape).astype(np.float32))
+    rb[0::3] = 0
+    xb[1::30] = rb[1::30]
+    c = cfgd(T, d, g, g, bits, k)
+    outs = []
+    for hint in HINTS:
+        say(f"[gpu] one row and strided forms {T}x{d} g={g} k={k} b={bits}: hint {hint}")
+        outs.append(gpu_run(dict(c, flags=c["flags"] | hint), xb, rb, None))
+    for o in outs[1:]:
+        for a, b in zip(outs[0], o):
+            assert np.array_equal(_bytes(a), _bytes(b))
+    ow, ox = oracle_run(c, xb, rb, None)
+    assert_parity(c, outs[0][0], outs[0][1], ow, ox)
