@@ -854,20 +854,17 @@ __device__ __forceinline__ uint64_t block_firsts(uint64_t x, int lv, uint64_t st
     return x & ~less;
 }
 
-// Chooses the k_g outliers of the lane's group and returns the lane's mask of
-// chosen channels (bit j = channel c0 + j).  k_g rounds, each taking the
+// Chooses the k_g outliers of the lane's group.  k_g rounds, each taking the
 // group's largest remaining |E| and, among the channels holding it, the
 // lowest.  Magnitudes are compared as the integer patterns of |E|, a chosen
 // channel drops to -1, so a zero residual still outranks it, and k_g < g_q
 // leaves every round a candidate.  The lanes holding the group maximum are
 // those whose own maximum equals it; the lowest of them in each group keeps
 // its lowest channel holding it, a scalar walk over the wave-wide masks of
-// the lanes whose channel j does.  The entries, (fp16 value | in-group offset
-// << 16), go to `st` at their position in the chunk's part of the row: group
-// by group, ascending offset inside a group.
+// the lanes whose channel j does.  sel[j] is the wave-wide mask of the lanes
+// whose channel j is chosen.
 template <int LV>
-__device__ __forceinline__ uint32_t select_group_outliers(const float* e, int lv, int kg, uint32_t lane,
-                                                          uint32_t* st) {
+__device__ __forceinline__ void choose_group_outliers(const float* e, int lv, int kg, uint64_t (&sel)[8]) {
     const int L = LV >= 0 ? LV : lv;
     int32_t a[8];
 #pragma unroll
@@ -886,9 +883,20 @@ __device__ __forceinline__ uint32_t select_group_outliers(const float* e, int lv
             lanes &= ~hit;
         }
     }
-    uint64_t sel[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) sel[j] = ballot(a[j] == -1);
+}
+
+// The same choice as the lane's mask of chosen channels (bit j = channel
+// c0 + j), with the entries, (fp16 value | in-group offset << 16), written to
+// `st` at their position in the chunk's part of the row: group by group,
+// ascending offset inside a group.
+template <int LV>
+__device__ __forceinline__ uint32_t select_group_outliers(const float* e, int lv, int kg, uint32_t lane,
+                                                          uint32_t* st) {
+    const int L = LV >= 0 ? LV : lv;
+    uint64_t sel[8];
+    choose_group_outliers<LV>(e, lv, kg, sel);
     uint32_t selm = 0u;
 #pragma unroll
     for (int j = 0; j < 8; ++j) selm |= __builtin_amdgcn_inverse_ballot_w64(sel[j]) ? (1u << j) : 0u;
@@ -2338,9 +2346,12 @@ __global__ __launch_bounds__(kErrThreads) void rac_error_kernel(const uint16_t* 
     }
 }
 
+// (block b: the partials of sample b, nparts after those of sample b - 1)
 __global__ __launch_bounds__(kErrThreads) void rac_error_final_kernel(const double* part, uint32_t nparts,
                                                                       double* out) {
     __shared__ double sh[3][kErrThreads];
+    part += (size_t)blockIdx.x * 3u * nparts;
+    out += (size_t)blockIdx.x * 3u;
     ErrSums v{0.0, 0.0, 0.0};
     for (uint32_t p = threadIdx.x; p < nparts; p += kErrThreads) {
         v.se = v.se + part[3u * p + 0u];
@@ -2352,6 +2363,176 @@ __global__ __launch_bounds__(kErrThreads) void rac_error_final_kernel(const doub
         out[0] = r.se;
         out[1] = r.sx;
         out[2] = r.mx;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Reconstruction error of many candidate configurations on one sample (the
+// calibration search).  A candidate's cost is known without encoding, so only
+// its error is computed: the fit, the outlier choice, the scales and the
+// quantizer of the encode, and the sums of the error kernel, all in registers;
+// neither a wire nor a reconstruction is written.  Candidates that differ only
+// in the bit width form a family, whose fit, outliers and group maxima are
+// computed once.  Workgroup (p, f) takes rows [8p, 8p + 8) for family f, one
+// wavefront per 512-channel chunk; groups (and per-group outliers) lie inside
+// a chunk, so no row needs a barrier.  Bound by vector issue: 1024 x 4096, 27
+// families of 4 widths, takes 282 us, where an encode, an error reduction and
+// its final block for each of the 108 candidates took 2900 us.
+// The sums' order is fixed whatever the device: a lane's channels row by row,
+// a butterfly over the lanes, then the wavefronts in order.
+constexpr int kEvalFamilies = 48;  // per launch
+
+struct EvalFamily {
+    int32_t cand[4];  // candidate of 2, 3, 4 and 8 bits, or -1
+    int32_t lv_a, lv_q, k, bf16;
+};
+
+struct EvalArgs {
+    const uint16_t* x;
+    const uint16_t* ref;
+    double* part;  // [candidate][parts][3]
+    uint32_t tokens, parts;
+    int32_t d, unused;
+    EvalFamily fam[kEvalFamilies];
+};
+
+template <int BITS>
+__device__ __forceinline__ void eval_width(const float* x, const float* ed, const float* rt, const uint64_t* sel,
+                                           bool outliers, bool bf16, float m, double& se, double& mx) {
+    constexpr float q = (float)((1 << (BITS - 1)) - 1);
+    const uint32_t sh = m == 0.0f ? 0u : scale_roundup(m, q, 1.0f / q);
+    const float s = f16_wire(sh);
+    float t[8], mg[8], qf[8], H[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = ed[j];
+    quantize8<BITS>(t, sh, s, false, mg, qf);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) H[j] = __builtin_fmaf(qf[j], s, rt[j]);
+    if (outliers) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) H[j] = __builtin_amdgcn_inverse_ballot_w64(sel[j]) ? rt[j] : H[j];
+    }
+    if (bf16) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) H[j] = __uint_as_float(bf16_rne(H[j]) << 16);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const double dd = (double)x[j] - (double)H[j];
+        se = se + dd * dd;
+        // (one instruction; the compiler's fmax first canonicalizes its operands)
+        asm("v_max_f64 %0, %0, |%1|" : "+v"(mx) : "v"(dd));
+    }
+}
+
+__global__ __launch_bounds__(kWave * kMaxWaves) void rac_eval_kernel(EvalArgs) {
+    __shared__ double red[kMaxWaves][9];
+    // (the arguments are read through the constant address space: the family
+    // is indexed by the block, the same for all its lanes)
+    using cargs = const __attribute__((address_space(4))) EvalArgs*;
+    const cargs A = (cargs)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const int w = (int)uniform(threadIdx.x / kWave);
+    const int waves = (int)(blockDim.x / kWave);
+    const uint32_t fi = blockIdx.y;
+    const int lv_a = A->fam[fi].lv_a, lv_q = A->fam[fi].lv_q, kg = A->fam[fi].k;
+    const bool bf16 = A->fam[fi].bf16 != 0;
+    const int32_t c2 = A->fam[fi].cand[0], c3 = A->fam[fi].cand[1], c4 = A->fam[fi].cand[2], c8 = A->fam[fi].cand[3];
+    const float inv_ga = __uint_as_float((uint32_t)(127 - 3 - lv_a) << 23);  // 1 / (8 * 2^lv_a)
+    const uint32_t row_bytes = (uint32_t)A->d * 2u, tokens = A->tokens;
+    const uint32_t off = ((uint32_t)w * kChunk + lane * 8u) * 2u;  // past the row: reads 0
+    for (uint32_t pt = blockIdx.x; pt < A->parts; pt += gridDim.x) {
+        const uint32_t row0 = pt * kErrRows, left = tokens - row0;
+        const uint32_t rows = left < (uint32_t)kErrRows ? left : (uint32_t)kErrRows;
+        double se[4] = {0.0, 0.0, 0.0, 0.0}, mx[4] = {0.0, 0.0, 0.0, 0.0}, sx = 0.0;
+        auto load = [&](uint32_t r, uint4& vx, uint4& vr) {
+            const bool in = r < rows;
+            const uint64_t o = (uint64_t)(row0 + (in ? r : 0u)) * (uint64_t)A->d;
+            vx = bload128(rsrc(A->x, o, in ? row_bytes : 0u), off);
+            vr = bload128(rsrc(A->ref, o, in && A->ref ? row_bytes : 0u), off);
+        };
+        uint4 nx, nr;
+        load(0u, nx, nr);
+        for (uint32_t r = 0; r < rows; ++r) {
+            float x[8], rt[8], e[8];
+            {
+                float rf[8], uu[8], uv[8];
+                widen8(nr, rf);
+                widen8(nx, x);
+                load(r + 1u, nx, nr);
+                const float mr = lane_sum(tree8(rf), lv_a) * inv_ga;
+                const float mxv = lane_sum(tree8(x), lv_a) * inv_ga;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float u = rf[j] - mr, v = x[j] - mxv;
+                    uu[j] = u * u;
+                    uv[j] = u * v;
+                }
+                const uint32_t cf = fit_coef(lane_sum(tree8(uu), lv_a), lane_sum(tree8(uv), lv_a), mr, mxv);
+                const float a = f16_wire(cf & 0xFFFFu), b0 = f16_wire(cf >> 16);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    rt[j] = __builtin_fmaf(a, rf[j], b0);
+                    e[j] = x[j] - rt[j];
+                }
+            }
+            uint64_t sel[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (kg > 0) {
+                // chosen channels: no residual, and R~ becomes their reconstruction
+                choose_group_outliers<-1>(e, lv_q, kg, sel);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool c = __builtin_amdgcn_inverse_ballot_w64(sel[j]);
+                    rt[j] = c ? rt[j] + f16_wire(f16_rne(e[j])) : rt[j];
+                    e[j] = c ? 0.0f : e[j];
+                }
+            }
+            float m = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(e[j]));
+            m = lane_max(m, lv_q);
+            if (c2 >= 0) eval_width<2>(x, e, rt, sel, kg > 0, bf16, m, se[0], mx[0]);
+            if (c3 >= 0) eval_width<3>(x, e, rt, sel, kg > 0, bf16, m, se[1], mx[1]);
+            if (c4 >= 0) eval_width<4>(x, e, rt, sel, kg > 0, bf16, m, se[2], mx[2]);
+            if (c8 >= 0) eval_width<8>(x, e, rt, sel, kg > 0, bf16, m, se[3], mx[3]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sx = sx + (double)x[j] * (double)x[j];
+        }
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            sx = sx + __shfl_xor(sx, o);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                se[i] = se[i] + __shfl_xor(se[i], o);
+                mx[i] = __builtin_fmax(mx[i], __shfl_xor(mx[i], o));
+            }
+        }
+        if (lane == 0u) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                red[w][i] = se[i];
+                red[w][4 + i] = mx[i];
+            }
+            red[w][8] = sx;
+        }
+        __syncthreads();
+        if (threadIdx.x < 4u) {
+            const int i = (int)threadIdx.x;
+            const int32_t c = i == 0 ? c2 : i == 1 ? c3 : i == 2 ? c4 : c8;
+            if (c >= 0) {
+                double a = red[0][i], b = red[0][8], t = red[0][4 + i];
+                for (int v = 1; v < waves; ++v) {
+                    a = a + red[v][i];
+                    b = b + red[v][8];
+                    t = __builtin_fmax(t, red[v][4 + i]);
+                }
+                double* const o = A->part + ((size_t)c * A->parts + pt) * 3u;
+                o[0] = a;
+                o[1] = b;
+                o[2] = t;
+            }
+        }
+        __syncthreads();  // the next part reuses red
     }
 }
 
@@ -2998,6 +3179,15 @@ bool error_args_ok(int64_t tokens, int32_t hidden, uint32_t flags) {
            (flags & ~uint32_t(RAC_FLAG_XHAT_BF16)) == 0 && (uint64_t)tokens * (uint64_t)hidden < (1ull << 40);
 }
 
+// The last launch of the error reduction: `samples` results of P partials each.
+rac_status run_error_final(const double* part, uint32_t P, uint32_t samples, double* stats, hipStream_t stream) {
+    void* b[] = {(void*)&part, (void*)&P, (void*)&stats};
+    return hipLaunchKernel(reinterpret_cast<const void*>(rac_error_final_kernel), dim3(samples), dim3(kErrThreads), b,
+                           0, stream) == hipSuccess
+               ? RAC_OK
+               : RAC_ERR_HIP;
+}
+
 // The two launches of the error reduction, with `part` holding err_parts(T)
 // partials (3 doubles each).
 rac_status run_error(int64_t tokens, int32_t hidden, uint32_t flags, const void* x, const void* xhat,
@@ -3013,12 +3203,7 @@ rac_status run_error(int64_t tokens, int32_t hidden, uint32_t flags, const void*
                             stream) != hipSuccess)
             return RAC_ERR_HIP;
     }
-    uint32_t np = P;
-    void* b[] = {(void*)&part, (void*)&np, (void*)&stats};
-    if (hipLaunchKernel(reinterpret_cast<const void*>(rac_error_final_kernel), dim3(1), dim3(kErrThreads), b, 0,
-                        stream) != hipSuccess)
-        return RAC_ERR_HIP;
-    return RAC_OK;
+    return run_error_final(part, P, 1, stats, stream);
 }
 
 rac_status check_error_call(int64_t tokens, int32_t hidden, uint32_t flags, const void* x, const void* xhat,
@@ -3057,6 +3242,61 @@ bool calib_space(const rac_candidate* c, int32_t n, CalibSpace* out) {
     out->stats = out->part + up256(err_parts(c[0].cfg.tokens) * 24u);
     out->total = out->stats + up256((uint64_t)n * 24u);
     return true;
+}
+
+// Candidates whose error rac_eval_kernel computes: every group (and with it
+// the outlier choice) inside a chunk, no outliers or per-group ones.
+bool eval_direct(const rac_config& c) {
+    return c.group_align <= kChunk && c.group_quant <= kChunk && (c.outlier_k == 0 || grouped(&c));
+}
+
+// Error sums of every eval_direct candidate into sums[3 * candidate], with
+// `part` holding n * P * 3 doubles.  The sums of the other candidates are left
+// unspecified.
+rac_status run_eval(const void* x, const void* ref, const rac_candidate* c, int32_t n, double* part, double* sums,
+                    hipStream_t stream) {
+    const uint32_t P = (uint32_t)err_parts(c[0].cfg.tokens);
+    EvalArgs A{};
+    A.x = static_cast<const uint16_t*>(x);
+    A.ref = static_cast<const uint16_t*>(ref);
+    A.part = part;
+    A.tokens = (uint32_t)c[0].cfg.tokens;
+    A.parts = P;
+    A.d = c[0].cfg.hidden;
+    const uint32_t threads = (uint32_t)((A.d + kChunk - 1) / kChunk) * kWave;
+    const uint32_t grid = P < kMaxDispatchItems / threads ? P : kMaxDispatchItems / threads;
+    int nf = 0;
+    auto flush = [&]() {
+        if (nf == 0 || P == 0) return RAC_OK;
+        void* a[] = {&A};
+        const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(rac_eval_kernel), dim3(grid, (unsigned)nf),
+                                             dim3(threads), a, 0, stream);
+        nf = 0;
+        return e == hipSuccess ? RAC_OK : RAC_ERR_HIP;
+    };
+    for (int32_t i = 0; i < n; ++i) {
+        const rac_config& k = c[i].cfg;
+        if (!eval_direct(k)) continue;
+        const int width = k.bits == 8 ? 3 : k.bits - 2;
+        const EvalFamily want{{-1, -1, -1, -1}, ilog2(k.group_align / 8), ilog2(k.group_quant / 8), k.outlier_k,
+                              (k.flags & RAC_FLAG_XHAT_BF16) ? 1 : 0};
+        int f = 0;
+        while (f < nf && !(A.fam[f].lv_a == want.lv_a && A.fam[f].lv_q == want.lv_q && A.fam[f].k == want.k &&
+                           A.fam[f].bf16 == want.bf16 && A.fam[f].cand[width] < 0))
+            ++f;
+        if (f == nf) {
+            if (nf == kEvalFamilies) {
+                const rac_status st = flush();
+                if (st != RAC_OK) return st;
+                f = 0;
+            }
+            A.fam[f] = want;
+            nf = f + 1;
+        }
+        A.fam[f].cand[width] = i;
+    }
+    const rac_status st = flush();
+    return st == RAC_OK ? run_error_final(part, P, (uint32_t)n, sums, stream) : st;
 }
 
 }  // namespace
@@ -3134,8 +3374,22 @@ rac_status rac_calibrate(const void* x, const void* ref, rac_candidate* candidat
     double* part = reinterpret_cast<double*>(ws + sp.part);
     double* sums = reinterpret_cast<double*>(ws + sp.stats);
     const uint64_t cap = sp.part - sp.wire;
+    // The error of candidates whose groups lie inside a chunk is computed
+    // directly, all of them in one pass over the sample, with the partials in
+    // the space of the reconstruction and the wire; the others are encoded and
+    // measured one by one (and take more than a few thousand candidates of a
+    // narrow sample, whose partials would not fit).
+    int32_t direct = 0;
+    for (int32_t i = 0; i < n; ++i) direct += eval_direct(candidates[i].cfg) ? 1 : 0;
+    const bool use_eval = direct > 0 && n <= 65536 &&
+                          (uint64_t)n * err_parts(candidates[0].cfg.tokens) * 24u <= sp.part;
+    if (use_eval) {
+        const rac_status st = run_eval(x, ref, candidates, n, reinterpret_cast<double*>(ws), sums, stream);
+        if (st != RAC_OK) return st;
+    }
     for (int32_t i = 0; i < n; ++i) {
         const rac_config& c = candidates[i].cfg;
+        if (use_eval && eval_direct(c)) continue;
         rac_status st = run_encode(&c, x, ref, nullptr, wire, cap, xh, stream, false, 0, nullptr);
         if (st != RAC_OK) return st;
         st = run_error(c.tokens, c.hidden, c.flags & RAC_FLAG_XHAT_BF16, x, xh, sums + 3 * i, part, stream);

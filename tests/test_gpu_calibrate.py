@@ -125,3 +125,41 @@ def test_calibration_with_bf16_reconstructions_and_zero_reference():
     xb, _, _ = wl.prefill_uplink(3, rows=(0, T), hidden=d)
     configs = [rac.RacConfig(T, d, g, g, b, 2, rac.RAC_FLAG_XHAT_BF16) for g in (64, 128) for b in (3, 4, 8)]
     _run(xb, None, configs, "zero reference, bf16 H-hat")
+
+
+@pytest.mark.parametrize("T,d,groups,zero_ref,scale", [
+    (29, 4096, (8, 16, 64, 512), False, 1.0),    # whole chunks, a part of 5 rows
+    (8, 1544, (8,), False, 1.0),                 # a ragged last chunk (1544 = 3 x 512 + 8)
+    (3, 512, (32, 128, 256), True, 1.0),         # one chunk, no reference
+    (17, 2048, (128, 256), False, 2.0e6),        # saturated scales and coefficients
+    (9, 8192, (64, 512), False, 1.0)])           # the widest rows
+def test_calibration_equals_encode_and_error_of_each_candidate(T, d, groups, zero_ref, scale):
+    """The search computes the error of candidates whose groups lie inside a
+    512-channel chunk without encoding them; every measurement must be that of
+    rac_encode followed by rac_recon_error (the sums in another order, the
+    maximum exactly), also where both kinds of candidate, duplicates and more
+    families than one launch holds share a call."""
+    import torch
+    say(f"[gpu] calibration against encode + error, {T}x{d} groups {groups} zero_ref={zero_ref} scale={scale}")
+    src = wl.prefill_uplink(5, rows=(0, T), hidden=d) if d % 128 == 0 else wl.affine_pair(wl.AffineRecipe(T, d, 8), 5)
+    x = to_dev(wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(src[0]) * np.float32(scale)))
+    ref = None if zero_ref else to_dev(src[1])
+    configs = [rac.RacConfig(T, d, ga, gq, b, k, (GRP if k else 0) | fl)
+               for fl in (0, rac.RAC_FLAG_XHAT_BF16) for ga in groups for gq in groups for b in (2, 3, 4, 8)
+               for k in (0, 1, 2, 7, 16) if gq <= 256 and k <= gq // 4 or k == 0]
+    configs += [configs[0], configs[1],
+                rac.RacConfig(T, d, groups[0], groups[0], 4, 3),                       # per-token outliers
+                rac.RacConfig(T, d, groups[-1], groups[0], 3, 0, rac.RAC_FLAG_LAUNCH_PER_ROW)]
+    if d & (d - 1) == 0:
+        configs.append(rac.RacConfig(T, d, d, d, 8, 0))                                # groups wider than a chunk
+    _, got = rac.rac_calibrate(x, ref, configs, 1e-3)
+    st = torch.empty(3, dtype=torch.float64, device="cuda")
+    ws = torch.empty(rac.rac_recon_error_workspace(T), dtype=torch.uint8, device="cuda")
+    for c, g in zip(configs, got):
+        bf16 = bool(c.flags & rac.RAC_FLAG_XHAT_BF16)
+        xh = torch.empty((T, d), dtype=torch.int16 if bf16 else torch.float32, device="cuda")
+        wire = torch.empty(rac.rac_wire_size(c), dtype=torch.uint8, device="cuda")
+        rac.rac_encode(c, x, ref, None, wire, xh)
+        rac.rac_recon_error(T, d, x, xh, st, ws, c.flags & rac.RAC_FLAG_XHAT_BF16)
+        se, sx, mx = st.cpu().numpy().tolist()
+        assert _close(g["sq_err"], se) and _close(g["sq_x"], sx) and g["max_abs"] == mx, (c, g, (se, sx, mx))
