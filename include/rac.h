@@ -117,14 +117,15 @@ enum {
     RAC_FLAG_GROUP_OUTLIERS = 1u << 2,
     /* Launch hints; neither changes the wire or any result, only how rows are
      * spread over workgroups, and neither is recorded in the wire.  By default
-     * an encode with per-token outliers of up to 4096 channels runs one
-     * workgroup per row; other calls of more than 256 rows run on a grid of
-     * the workgroups the device holds at once, each taking rows in strides
-     * with its next row prefetched, unless that would give each more than six
-     * rows (four for wider rows with per-token outliers); then one workgroup
-     * per row (over many rows the strided workgroups drift apart and the HBM
-     * writes lose locality).  STRIDED always takes the strided grid, PER_ROW
-     * always one workgroup per row; setting both is RAC_ERR_INVALID. */
+     * an encode hands its rows out in order (a workgroup per row, or a
+     * wavefront per 512 channels of a row); a decode, and an encode whose rows
+     * are wider than 4096 channels (per-token outliers) or whose groups or
+     * step table make a row's wavefronts meet, run more than 256 rows on a
+     * grid of the workgroups the device holds at once, each taking rows in
+     * strides with its next row prefetched, while that gives each only a few
+     * (three to six) rows: over many rows the strided workgroups drift apart
+     * and the HBM writes lose locality.  STRIDED always takes the strided
+     * grid, PER_ROW always rows in order; setting both is RAC_ERR_INVALID. */
     RAC_FLAG_LAUNCH_STRIDED = 1u << 3,
     RAC_FLAG_LAUNCH_PER_ROW = 1u << 4
 };

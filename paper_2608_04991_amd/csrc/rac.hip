@@ -44,10 +44,12 @@ constexpr int kChunk = 512;       // channels per wavefront (8 per lane)
 constexpr int kMaxWaves = 16;     // rows up to 8192 channels
 constexpr int kCandCap = 64;      // outlier candidates ranked by one wavefront (twice that for k > 48)
 constexpr int kMaxGatherRows = 64; // rows per workgroup with a gathered reference
+constexpr int kFlatWaves = 4;      // wavefronts per workgroup where each takes one (row, chunk)
 // Launch shape (see launch): beyond this many rows per resident workgroup, one
 // workgroup per row
 constexpr int kStridedRowsMax = 6;
 constexpr int kWideStridedRowsMax = 4;
+constexpr int kDecodeStridedRowsMax = 3;
 constexpr int kManyRows = 8192;
 constexpr size_t kSevenPerCu = 2560;  // LDS bytes that keep an eighth workgroup off a compute unit
 constexpr uint32_t kMaxDispatchItems = 0xFFFFFFFFu;  // work-items one dispatch holds (per dimension)
@@ -82,6 +84,7 @@ struct alignas(8) Args {
     int32_t d;
     int32_t code_row_bytes;  // d * bits / 8
     int32_t nch;        // 512-channel chunks per row = wavefronts per workgroup
+    uint32_t nch_magic; // ceil(2^32 / nch): the high word of its product with i < 2^26 is i / nch (nch > 1)
     int32_t lg_a, lg_q; // log2 of the group sizes
     int32_t lane_lv_a;  // butterfly levels inside a chunk: log2(min(g, 512) / 8)
     int32_t lane_lv_q;
@@ -727,10 +730,12 @@ __device__ __forceinline__ int32_t ref_index_v(const Args& A, int32_t cache, uin
 // address space (the array is read-only for the whole launch): that makes it a
 // scalar load, which is waited for apart from the vector loads, and the kernels
 // issue it first, before any store or barrier.
-__device__ __forceinline__ int32_t first_ref_index(const Args& A) {
+__device__ __forceinline__ int32_t ref_index_s(const Args& A, uint32_t row) {
     using cptr = const __attribute__((address_space(4))) int32_t*;
-    return (A.ref_rows && blockIdx.x < A.tokens) ? ((cptr)A.ref_rows)[blockIdx.x] : 0;
+    return (A.ref_rows && row < A.tokens) ? ((cptr)A.ref_rows)[row] : 0;
 }
+
+__device__ __forceinline__ int32_t first_ref_index(const Args& A) { return ref_index_s(A, blockIdx.x); }
 
 // Buffer resource of token row `row`'s reference: row `row` of ref, or, with
 // a row index array, store row `ix`.  A missing reference, a row past the
@@ -1107,25 +1112,41 @@ __device__ __forceinline__ uint32_t select_outliers(const Args& A, RowShared& S,
 // chunk with that many butterfly levels, 7 = groups spanning chunks, -1 =
 // read from the arguments at run time.  OM is the outlier mode: 0 none, 1 the
 // k largest |E| per token row, 2 the k_g largest per quantization group.
-template <int BITS, int GA, int GQ, int OM>
-__global__ __launch_bounds__(kWave * kMaxWaves) __attribute__((amdgpu_waves_per_eu(OM == 2 && GQ >= 0 ? 6 : 1)))
+// FLAT: workgroups of kFlatWaves wavefronts that take one (row, chunk) each, in
+// row order, and no next row.  Without per-token outliers and with groups
+// inside a chunk no two wavefronts of a row meet, so a row need not be one
+// workgroup: rows of many chunks then leave no wavefront slots empty between
+// workgroups (at 80 registers a compute unit holds one 16-wavefront row of
+// 8192 channels, two thirds of its slots).
+template <int BITS, int GA, int GQ, int OM, bool FLAT = false>
+__global__ __launch_bounds__(FLAT ? kWave * kFlatWaves : kWave * kMaxWaves)
+__attribute__((amdgpu_waves_per_eu(OM == 2 && GQ >= 0 ? (FLAT ? 7 : 6) : 1)))
 void rac_encode_kernel(Args A) {
     // LDS state of a row, double-buffered by row parity: every row that uses
     // LDS has a workgroup barrier, so no wave is more than one row ahead.
     __shared__ RowShared SS[2];
     extern __shared__ float4 XT[];  // per-wavefront store staging, kSlice each (sized at launch)
     const uint32_t lane = threadIdx.x & (kWave - 1);
-    const int w = (int)(threadIdx.x / kWave);
+    const int wl = (int)(threadIdx.x / kWave);
+    int w = wl;
+    uint32_t row = blockIdx.x;
+    if constexpr (FLAT) {
+        static_assert(OM != 1 && GA != 7 && GQ != 7, "wavefronts of a row do not meet");
+        const uint32_t id = blockIdx.x * kFlatWaves + uniform((uint32_t)wl);
+        row = A.nch == 1 ? id : __umulhi(id, A.nch_magic);  // id / nch
+        w = (int)(id - row * (uint32_t)A.nch);
+        if (row >= A.tokens) return;
+    }
     const int d = A.d;
     const int c0 = w * kChunk + (int)lane * 8;
     const bool act = c0 < d;
     constexpr float q = (float)((1 << (BITS - 1)) - 1);
     constexpr float inv_q = 1.0f / q;
-    const int32_t fix = first_ref_index(A);  // store row of the first row's reference
-    if (A.write_header && blockIdx.x == 0 && w == 0) write_header(A, lane);
+    const int32_t fix = FLAT ? ref_index_s(A, row) : first_ref_index(A);  // store row of the first row's reference
+    if (A.write_header && blockIdx.x == 0 && wl == 0) write_header(A, lane);
     const bool dword3 = (d & 31) == 0;
-    const bool multi_a = GA == 7 || (GA < 0 && A.lg_cpg_a > 0);
-    const bool multi_q = GQ == 7 || (GQ < 0 && A.lg_cpg_q > 0);
+    const bool multi_a = GA == 7 || (GA < 0 && !FLAT && A.lg_cpg_a > 0);
+    const bool multi_q = GQ == 7 || (GQ < 0 && !FLAT && A.lg_cpg_q > 0);
     const int lv_a = GA >= 0 ? (GA == 7 ? 6 : GA) : A.lane_lv_a;
     const int lv_q = GQ >= 0 ? (GQ == 7 ? 6 : GQ) : A.lane_lv_q;
     const int grp_a = c0 >> A.lg_a, grp_q = c0 >> A.lg_q;
@@ -1160,18 +1181,17 @@ void rac_encode_kernel(Args A) {
         vx = bload128(rsrc(A.x, o, in ? row_bytes : 0u), (uint32_t)c0 * 2u);
         vr = bload128(ref_row(A, rw, in, ix), (uint32_t)c0 * 2u);
     };
-    uint32_t row = blockIdx.x;
     uint4 nx, nr;
-    const int32_t rix = load_ref_rows_v(A, lane);  // store rows of the gathered reference
+    const int32_t rix = FLAT ? 0 : load_ref_rows_v(A, lane);  // store rows of the gathered reference
     load_row(row, fix, nx, nr);
     // Let the first row land before the loop: then the loop head holds no
     // wait, and inside the loop only the prefetched loads are waited for
     // (never the stores of the row before).
-    __builtin_amdgcn_s_waitcnt(kWaitVmem0);
+    if constexpr (!FLAT) __builtin_amdgcn_s_waitcnt(kWaitVmem0);
     for (uint32_t n = 0; row < A.tokens; row += gridDim.x, ++n) {
         RowShared& S = SS[n & 1];
         const uint4 xv = nx, rv = nr;
-        load_row(row + gridDim.x, ref_index_v(A, rix, n + 1u), nx, nr);
+        if constexpr (!FLAT) load_row(row + gridDim.x, ref_index_v(A, rix, n + 1u), nx, nr);
         float r[8], x[8];
         widen8(rv, r);
         widen8(xv, x);
@@ -1233,7 +1253,7 @@ void rac_encode_kernel(Args A) {
         uint32_t selm = 0;
         if constexpr (OM == 1) selm = select_outliers(A, S, SS[(n + 1) & 1], e, act, c0, lane, w, row);
         if constexpr (OM == 2) {
-            uint32_t* st = reinterpret_cast<uint32_t*>(XT + w * kSlice);
+            uint32_t* st = reinterpret_cast<uint32_t*>(XT + wl * kSlice);
             selm = select_group_outliers<GQ>(e, lv_q, A.k, lane, st);
             wave_lds_sync();
             store_group_outliers(rsrc(A.gval, (uint64_t)row * gent, gent * 2u), rsrc(A.goff, (uint64_t)row * gent, gent),
@@ -1291,7 +1311,8 @@ void rac_encode_kernel(Args A) {
         }
         const uint32_t crb = (uint32_t)A.code_row_bytes;
         store_codes<BITS>(rsrc(A.codes, (uint64_t)row * crb, crb), w, lane, dword3, pk);
-        store_xhat_t(xhat_row(A, row), A.xhat_bf16 != 0, (uint32_t)(w * kChunk), lane, XT + w * kSlice, H);
+        store_xhat_t(xhat_row(A, row), A.xhat_bf16 != 0, (uint32_t)(w * kChunk), lane, XT + wl * kSlice, H);
+        if constexpr (FLAT) return;
     }
 }
 
@@ -2623,6 +2644,7 @@ Args make_args(const rac_config* c, const Sizes& S) {
     A.tokens = (uint32_t)c->tokens;
     A.d = c->hidden;
     A.nch = (c->hidden + kChunk - 1) / kChunk;
+    A.nch_magic = (uint32_t)(((1ull << 32) + (uint64_t)A.nch - 1u) / (uint64_t)A.nch);
     A.lg_a = ilog2(c->group_align);
     A.lg_q = ilog2(c->group_quant);
     A.lane_lv_a = ilog2(c->group_align >= kChunk ? kChunk / 8 : c->group_align / 8);
@@ -2683,20 +2705,36 @@ void fill_header(Args& A, const rac_config* c, bool zero_ref, bool pooled = fals
 
 using KernelFn = void (*)(Args);
 
+// A kernel in its launch shapes: `fn` takes rows in strides of the grid (or one
+// row per workgroup), `one` (may be null) only ever one: a row per workgroup,
+// or with `flat` a (row, chunk) per wavefront.
+struct Kernels {
+    KernelFn fn, one;
+    bool flat;
+};
+
+template <int BITS, int GA, int GQ, int OM>
+Kernels encode_pair() {
+    if constexpr (OM != 1 && GQ != 7)
+        return {rac_encode_kernel<BITS, GA, GQ, OM>, rac_encode_kernel<BITS, GA, GQ, OM, true>, true};
+    else
+        return {rac_encode_kernel<BITS, GA, GQ, OM>, nullptr, false};
+}
+
 template <int GA, int GQ, int OM>
-KernelFn encode_for_bits(int bits) {
+Kernels encode_for_bits(int bits) {
     switch (bits) {
-        case 2: return rac_encode_kernel<2, GA, GQ, OM>;
-        case 3: return rac_encode_kernel<3, GA, GQ, OM>;
-        case 4: return rac_encode_kernel<4, GA, GQ, OM>;
-        default: return rac_encode_kernel<8, GA, GQ, OM>;
+        case 2: return encode_pair<2, GA, GQ, OM>();
+        case 3: return encode_pair<3, GA, GQ, OM>();
+        case 4: return encode_pair<4, GA, GQ, OM>();
+        default: return encode_pair<8, GA, GQ, OM>();
     }
 }
 
 // (groups spanning chunks, GQ = 7, exceed the 256 channels of per-group
 // outliers, so that form has no mode 2)
 template <int GA, int GQ>
-KernelFn encode_for(int bits, int om) {
+Kernels encode_for(int bits, int om) {
     if constexpr (GQ != 7) {
         if (om == 2) return encode_for_bits<GA, GQ, 2>(bits);
     }
@@ -2707,8 +2745,8 @@ int outlier_mode(const Args& A) { return A.gout ? 2 : (A.k > 0 ? 1 : 0); }
 
 // Specialized group shapes: 64/64, 128/128, the mixed 64/128 and 128/64, and
 // 128 with one scale per row of up to 8192 channels; anything else takes the
-// generic kernel.
-KernelFn pick_encode(const Args& A, int bits) {
+// generic kernel, whose wavefronts meet where a group spans chunks.
+Kernels pick_encode(const Args& A, int bits) {
     const int ga = A.lg_cpg_a > 0 ? 7 : A.lane_lv_a;
     const int gq = A.lg_cpg_q > 0 ? 7 : A.lane_lv_q;
     const int om = outlier_mode(A);
@@ -2717,28 +2755,26 @@ KernelFn pick_encode(const Args& A, int bits) {
     if (ga == 3 && gq == 4) return encode_for<3, 4>(bits, om);
     if (ga == 4 && gq == 3) return encode_for<4, 3>(bits, om);
     if (ga == 4 && gq == 7) return encode_for<4, 7>(bits, om);
-    return encode_for<-1, -1>(bits, om);
+    Kernels k = encode_for<-1, -1>(bits, om);
+    if (ga == 7 || gq == 7) k.one = nullptr;
+    return k;
 }
 
 // The rows kernel in its two launch shapes: workgroups that take rows in
 // strides of the grid, and one workgroup per row (null with given pairs, whose
 // search for the row's segment the strided form overlaps with the row before:
 // 4096 x 4096 pooled 43.5 us strided, 47.0 with one workgroup per row).
-struct RowsKernels {
-    KernelFn strided, one;
-};
-
 template <int BITS, int GA, int GQ, int CPW, bool GIVEN, bool TWO, bool BIG>
-RowsKernels rows_pair() {
+Kernels rows_pair() {
     if constexpr (GIVEN)
-        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, true, TWO, BIG>, nullptr};
+        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, true, TWO, BIG>, nullptr, false};
     else
         return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG>,
-                rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG, true>};
+                rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG, true>, false};
 }
 
 template <int GA, int GQ, int CPW, bool GIVEN, bool TWO, bool BIG>
-RowsKernels rows_for_bits(int bits) {
+Kernels rows_for_bits(int bits) {
     switch (bits) {
         case 2: return rows_pair<2, GA, GQ, CPW, GIVEN, TWO, BIG>();
         case 3: return rows_pair<3, GA, GQ, CPW, GIVEN, TWO, BIG>();
@@ -2748,7 +2784,7 @@ RowsKernels rows_for_bits(int bits) {
 }
 
 template <int GA, int GQ, int CPW, bool GIVEN>
-RowsKernels rows_for_cpw(int bits, int k) {
+Kernels rows_for_cpw(int bits, int k) {
     if constexpr (GIVEN) {
         return rows_for_bits<GA, GQ, CPW, true, false, false>(bits);
     } else {
@@ -2763,7 +2799,7 @@ RowsKernels rows_for_cpw(int bits, int k) {
 // candidate list beyond (not with given pairs, which keep the one-value
 // bound and the smaller list: every bound and list size is exact).
 template <int GA, int GQ, bool GIVEN = false>
-RowsKernels rows_for(int bits, int d, int k) {
+Kernels rows_for(int bits, int d, int k) {
     if (d <= kRowsWaves * 2 * kChunk) return rows_for_cpw<GA, GQ, 2, GIVEN>(bits, k);
     return rows_for_cpw<GA, GQ, 4, GIVEN>(bits, k);
 }
@@ -2775,7 +2811,7 @@ bool use_rows_kernel(const Args& A) {
     return outlier_mode(A) == 1 && !A.fixed && A.d <= kRowsMaxD && A.lg_cpg_a == 0 && A.lg_cpg_q == 0;
 }
 
-RowsKernels pick_rows(const Args& A, int bits) {
+Kernels pick_rows(const Args& A, int bits) {
     // given pairs (pooled fit): the fixed 128 and 64 shapes and the generic one
     if (A.cf_given) {
         if (A.lane_lv_a == 4 && A.lane_lv_q == 4) return rows_for<4, 4, true>(bits, A.d, A.k);
@@ -2861,11 +2897,14 @@ rac_status device_cus(int* cus) {
 // flight spread over the tensors and the HBM writes lose locality; with one
 // workgroup per row the dispatcher hands rows out in order as workgroups
 // finish, which keeps them together.  Up to 256 rows every workgroup takes one
-// row; beyond that the shape is chosen by rows per resident workgroup, and the
-// launch flags of the configuration override the choice.
-//   - Kernels with one form only (`one` null): strided up to
-//     kStridedRowsMax.  At 65536 x 3584 one workgroup per row is 13% faster
-//     for the decode; at four rows per workgroup the two are even.
+// row; beyond that the shape is chosen by rows per resident workgroup
+// (`strided_max`), and the launch flags of the configuration override the
+// choice.
+//   - No outliers or per-group ones, groups inside a chunk (`one`, flat):
+//     always a (row, chunk) per wavefront, in row order.  k_g = 2, us, strided
+//     and flat: 2048 x 2048 10.6 and 9.7, 4096 x 4096 34.7 and 29.1, 65536 x
+//     3584 433 and 344, 4096 x 8192 63.2 and 52.4; no outliers: 4096 x 4096
+//     28.8 and 26.9, 65536 x 3584 394 and 327.
 //   - Per-token outliers (`one`: the form that holds no next row), up to
 //     4096 channels: always one workgroup per row.  k = 8, us, strided and one
 //     per row: 2048 x 4096 18.1 and 15.8, 4096 x 4096 31.0 and 30.4, 16384 x
@@ -2877,8 +2916,16 @@ rac_status device_cus(int* cus) {
 //     workgroups a compute unit instead of eight, by LDS that is requested and
 //     not used: 65536 x 3584 339.8 against 350.6 us, 32768 x 4096 194.8
 //     against 197.5 (32768 x 2048, which stays at eight, 109.2 against 107.1).
-rac_status launch(KernelFn fn, Args A, hipStream_t stream, int threads = 0, int max_per_cu = 0,
-                  KernelFn one = nullptr) {
+//   - The decode: strided up to kDecodeStridedRowsMax; beyond 4096 channels
+//     up to kWideStridedRowsMax, with per-group outliers kStridedRowsMax.  us,
+//     strided and one per row: 3072 x 4096 16.9 and 16.8, 4096 x 4096 21.3 and
+//     20.8, 8192 x 4096 40.5 and 37.4, 2048 x 8192 21.1 and 21.2, 3072 x 8192
+//     30.9 and 29.5, with k_g = 2 31.2 and 34.5.
+//   - The other kernels (a row's wavefronts meet, one form): strided up to
+//     kStridedRowsMax.
+rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0, int max_per_cu = 0,
+                  int strided_max = kStridedRowsMax) {
+    KernelFn fn = k.fn;
     const int64_t rows = A.tokens;
     // kernels launched with one wavefront per chunk stage through a
     // dynamically sized slice per wavefront
@@ -2886,12 +2933,12 @@ rac_status launch(KernelFn fn, Args A, hipStream_t stream, int threads = 0, int 
     if (staged) threads = A.nch * kWave;
     size_t lds = staged ? (size_t)A.nch * kSlice * sizeof(float4) : 0;
     int64_t blocks = rows <= 0 ? 1 : rows;
-    const int64_t strided_max = !one ? kStridedRowsMax : A.nch > 2 * kRowsWaves ? kWideStridedRowsMax : 0;
+    if (k.one) strided_max = !k.flat && A.nch > 2 * kRowsWaves ? kWideStridedRowsMax : 0;
     if (rows > 256 && A.launch_shape != 2 && (strided_max > 0 || A.launch_shape == 1)) {
         int cus = 0, per_cu = 0;
         if (resident(reinterpret_cast<const void*>(fn), threads, lds, &cus, &per_cu) != RAC_OK) return RAC_ERR_HIP;
         const int64_t fits = (int64_t)cus * (per_cu > 0 ? per_cu : 1);  // workgroups the device holds at once
-        if (A.launch_shape == 1 || rows <= strided_max * fits) {
+        if (A.launch_shape == 1 || rows <= (int64_t)strided_max * fits) {
             if (max_per_cu > 0 && per_cu > max_per_cu) per_cu = max_per_cu;
             int64_t resident = (int64_t)cus * (per_cu > 0 ? per_cu : 1);
             // a gathered reference: at most kMaxGatherRows rows per workgroup,
@@ -2908,8 +2955,16 @@ rac_status launch(KernelFn fn, Args A, hipStream_t stream, int threads = 0, int 
     const int64_t max_blocks = (int64_t)(kMaxDispatchItems / (uint32_t)threads);
     if (blocks > max_blocks) blocks = max_blocks;
     if (A.ref_rows && blocks * kMaxGatherRows < rows) return RAC_ERR_UNSUPPORTED;
-    if (one && blocks == rows) {
-        fn = one;
+    if (k.one && k.flat && blocks == rows) {
+        const int64_t flat = (rows * A.nch + kFlatWaves - 1) / kFlatWaves;
+        if (flat <= (int64_t)(kMaxDispatchItems / (kFlatWaves * kWave))) {
+            fn = k.one;
+            blocks = flat;
+            threads = kFlatWaves * kWave;
+            lds = kFlatWaves * kSlice * sizeof(float4);
+        }
+    } else if (k.one && blocks == rows) {
+        fn = k.one;
         if (rows > kManyRows && A.k <= kTop1 && A.nch > kRowsWaves && A.nch <= 2 * kRowsWaves) lds = kSevenPerCu;
     }
     void* args[] = {&A};
@@ -2955,9 +3010,15 @@ rac_status run_decode(const rac_config* cfg, const void* wire, const void* ref, 
     A.store_rows = (uint32_t)store_rows;
     A.steps = steps;
     A.xhat = xhat;
-    // (with outliers, two workgroups per compute unit, each taking more rows,
-    // measured fastest: 4-8% below a full grid at 4096 x 4096 and 16384 x 3584)
-    return launch(pick_decode(A, cfg->bits), A, stream, 0, outlier_mode(A) == 1 ? 2 : 0);
+    // (with per-token outliers, 16 wavefronts per compute unit and at least two
+    // workgroups, each taking more rows, measured fastest: 4-8% below a full
+    // grid at 4096 x 4096 and 16384 x 3584)
+    const int per_cu = A.nch <= 8 ? 16 / A.nch : 2;
+    const int strided_max = A.nch <= 2 * kRowsWaves ? kDecodeStridedRowsMax
+                          : outlier_mode(A) == 2    ? kStridedRowsMax
+                                                    : kWideStridedRowsMax;
+    return launch({pick_decode(A, cfg->bits), nullptr, false}, A, stream, 0, outlier_mode(A) == 1 ? per_cu : 0,
+                  strided_max);
 }
 
 }  // namespace
@@ -3070,10 +3131,7 @@ rac_status run_encode(const rac_config* cfg, const void* x, const void* ref, con
     A.xhat = xhat;
     A.write_header = 1;
     fill_header(A, cfg, ref == nullptr);
-    if (use_rows_kernel(A)) {
-        const RowsKernels k = pick_rows(A, cfg->bits);
-        return launch(k.strided, A, stream, kRowsWaves * kWave, 0, k.one);
-    }
+    if (use_rows_kernel(A)) return launch(pick_rows(A, cfg->bits), A, stream, kRowsWaves * kWave);
     return launch(pick_encode(A, cfg->bits), A, stream);
 }
 
@@ -3151,10 +3209,7 @@ rac_status rac_encode_pooled(const rac_config* cfg, const void* x, const void* r
     A.cf_given = 1;
     A.write_header = 1;
     fill_header(A, cfg, ref == nullptr, true);
-    if (use_rows_kernel(A)) {
-        const RowsKernels k = pick_rows(A, cfg->bits);
-        return launch(k.strided, A, stream, kRowsWaves * kWave, 0, k.one);
-    }
+    if (use_rows_kernel(A)) return launch(pick_rows(A, cfg->bits), A, stream, kRowsWaves * kWave);
     return launch(pick_encode(A, cfg->bits), A, stream);
 }
 

@@ -197,3 +197,35 @@ def test_one_row_and_strided_forms_on_ties_and_plain_rows(d, g, k, bits):
             assert np.array_equal(_bytes(a), _bytes(b))
     ow, ox = oracle_run(c, xb, rb, None)
     assert_parity(c, outs[0][0], outs[0][1], ow, ox)
+
+
+@pytest.mark.parametrize("T,d,ga,gq,bits,k", [(1, 512, 64, 64, 4, 0), (257, 520, 8, 8, 3, 2), (333, 1536, 512, 256, 2, 16),
+                                              (301, 7168, 128, 64, 8, 1), (259, 8192, 64, 128, 4, 4),
+                                              (263, 4608, 256, 512, 3, 0)])
+def test_flat_and_strided_forms_of_the_chunk_kernel(T, d, ga, gq, bits, k):
+    # a (row, chunk) per wavefront against strided rows, plain, gathered (with
+    # rows that name no store row) and with a bf16 reconstruction: rows of 1 to
+    # 16 chunks, so that workgroups of four wavefronts straddle rows and the
+    # last one is partly empty
+    rng = np.random.default_rng([d, T])
+    xb, rb, _ = wl.prefill_uplink(12, tokens=T, hidden=d) if d % 128 == 0 else \
+        wl.affine_pair(wl.AffineRecipe(T, d, 8), 12)
+    idx = rng.permutation(T).astype(np.int32)
+    idx[rng.random(T) < 0.2] = -1
+    gathered = np.where(idx[:, None] >= 0, rb[np.maximum(idx, 0)], 0).astype(np.uint16)
+    import torch
+    for bf16 in (0, rac.RAC_FLAG_XHAT_BF16):
+        c = cfgd(T, d, ga, gq, bits, k, (GRP if k else 0) | bf16)
+        ow, ox = oracle_run(c, xb, rb, None)
+        gw, gx = oracle_run(c, xb, gathered, None)
+        for hint in HINTS:
+            say(f"[gpu] flat and strided {T}x{d} g={ga}/{gq} b={bits} k_g={k} bf16={bf16}: hint {hint}")
+            out = gpu_run(dict(c, flags=c["flags"] | hint), xb, rb, None)
+            assert_parity(c, out[0], out[1], ow, ox)
+            cfg = rac.RacConfig(**dict(c, flags=c["flags"] | hint))
+            wire = torch.empty(rac.rac_wire_size(cfg), dtype=torch.uint8, device="cuda")
+            xh = torch.empty((T, d), dtype=torch.int16 if bf16 else torch.float32, device="cuda")
+            rac.rac_encode_gather(cfg, to_dev(xb), to_dev(rb), torch.from_numpy(idx).cuda(), None, wire, xh)
+            torch.cuda.synchronize()
+            assert np.array_equal(wire.cpu().numpy(), _bytes(gw).ravel())
+            assert np.array_equal(_bytes(xh.cpu().numpy()), _bytes(gx))
