@@ -32,30 +32,46 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Wall", "-Wno-unused-function"]
 
 
+PARTS = (None, 2, 3, 4, 8)  # rac.hip: everything but the per-width kernels, then one bit width each
+
+
 def build(verbose: bool = True) -> str:
-    os.makedirs(os.path.dirname(LIB), exist_ok=True)
+    out = os.path.dirname(LIB)
+    os.makedirs(out, exist_ok=True)
+    compile_flags = [f for f in FLAGS if f != "-shared"]
+    # every object, and the device assembly of the codec's parts that is
+    # scanned, are independent compiles: run them side by side
+    jobs, objs, asms = [], [], []
+    for part in PARTS:
+        define = [] if part is None else [f"-DRAC_PART={part}"]
+        name = os.path.join(out, f"rac_{part or 'main'}")
+        objs.append(name + ".o")
+        asms.append(name + ".s")
+        jobs.append([HIPCC, *compile_flags, *define, "-c", "-I", INC, "-o", objs[-1], SRC])
+        jobs.append([HIPCC, *[f for f in compile_flags if f != "-fPIC"], *define, "--cuda-device-only", "-S",
+                     "-I", INC, "-o", asms[-1], SRC])
+    for src in (PRED_SRC, HOST_SRC):
+        objs.append(os.path.join(out, os.path.basename(src) + ".o"))
+        jobs.append([HIPCC, *compile_flags, "-c", "-I", INC, "-o", objs[-1], src])
     tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-I", INC, "-o", tmp, SRC, PRED_SRC, HOST_SRC]
-    asm = LIB + ".s"
-    dev = [HIPCC, *[f for f in FLAGS if f not in ("-fPIC", "-shared")], "--cuda-device-only", "-S",
-           "-I", INC, "-o", asm, SRC]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    # the library and the device assembly that is scanned are independent
-    # compiles: run them side by side
-    procs = [subprocess.Popen(cmd), subprocess.Popen(dev)]
-    codes = [p.wait() for p in procs]
-    if any(codes):
-        for f in (tmp, asm):
+    try:
+        if verbose:
+            for cmd in jobs:
+                print(" ".join(cmd), flush=True)
+        procs = [subprocess.Popen(cmd) for cmd in jobs]
+        codes = [p.wait() for p in procs]
+        for code, cmd in zip(codes, jobs):
+            if code:
+                raise subprocess.CalledProcessError(code, cmd)
+        bad = [hit for asm in asms for hit in isa_check.scan(open(asm).read())]
+        if bad:
+            raise RuntimeError("miscompiled SCC use in librac:\n" + "\n".join(bad))
+        subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
+        os.replace(tmp, LIB)
+    finally:
+        for f in (tmp, *objs, *asms):
             if os.path.exists(f):
                 os.remove(f)
-        raise subprocess.CalledProcessError(next(c for c in codes if c), cmd if codes[0] else dev)
-    bad = isa_check.scan(open(asm).read())
-    os.remove(asm)
-    if bad:
-        os.remove(tmp)
-        raise RuntimeError("miscompiled SCC use in librac:\n" + "\n".join(bad))
-    os.replace(tmp, LIB)
     return LIB
 
 

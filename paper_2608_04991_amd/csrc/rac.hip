@@ -37,6 +37,13 @@
 
 #include "rac.h"
 
+// A part's kernels for a call: `args` is the call's Args, `out` gets Kernels.
+#define RAC_PART_FN(bits) __attribute__((visibility("hidden"))) void rac_part_kernels_##bits(int kind, const void* args, void* out)
+RAC_PART_FN(2);
+RAC_PART_FN(3);
+RAC_PART_FN(4);
+RAC_PART_FN(8);
+
 namespace {
 
 constexpr int kWave = 64;
@@ -2121,6 +2128,24 @@ __global__ __launch_bounds__(kWave * kMaxWaves) void rac_decode_kernel(Args A) {
 }
 
 // ---------------------------------------------------------------------------
+// Choice of the kernels for a call (host)
+
+using KernelFn = void (*)(Args);
+
+// A kernel in its launch shapes: `fn` takes rows in strides of the grid (or one
+// row per workgroup), `one` (may be null) only ever one: a row per workgroup,
+// or with `flat` a (row, chunk) per wavefront.
+struct Kernels {
+    KernelFn fn, one;
+    bool flat;
+};
+
+enum KernelKind { kEncodeKernels, kRowsKernels, kDecodeKernels };
+
+int outlier_mode(const Args& A) { return A.gout ? 2 : (A.k > 0 ? 1 : 0); }
+
+#ifndef RAC_PART
+// ---------------------------------------------------------------------------
 // Fit pooled over segments of rows (the affine-fit equation over all fitting
 // positions of a segment).  Three launches: the per-(row, group) centred
 // moments, their merge over each segment, then the encode with the merged
@@ -2703,105 +2728,18 @@ void fill_header(Args& A, const rac_config* c, bool zero_ref, bool pooled = fals
                    ((uint32_t)h[4 * i + 3] << 24);
 }
 
-using KernelFn = void (*)(Args);
-
-// A kernel in its launch shapes: `fn` takes rows in strides of the grid (or one
-// row per workgroup), `one` (may be null) only ever one: a row per workgroup,
-// or with `flat` a (row, chunk) per wavefront.
-struct Kernels {
-    KernelFn fn, one;
-    bool flat;
-};
-
-template <int BITS, int GA, int GQ, int OM>
-Kernels encode_pair() {
-    if constexpr (OM != 1 && GQ != 7)
-        return {rac_encode_kernel<BITS, GA, GQ, OM>, rac_encode_kernel<BITS, GA, GQ, OM, true>, true};
-    else
-        return {rac_encode_kernel<BITS, GA, GQ, OM>, nullptr, false};
-}
-
-template <int GA, int GQ, int OM>
-Kernels encode_for_bits(int bits) {
+// The kernels of each bit width are instantiated in a part of their own (this
+// file compiled with RAC_PART = 2, 3, 4 or 8, see the end), so that the parts
+// compile side by side.
+Kernels pick_kernels(KernelKind kind, const Args& A, int bits) {
+    Kernels k{};
     switch (bits) {
-        case 2: return encode_pair<2, GA, GQ, OM>();
-        case 3: return encode_pair<3, GA, GQ, OM>();
-        case 4: return encode_pair<4, GA, GQ, OM>();
-        default: return encode_pair<8, GA, GQ, OM>();
+        case 2: rac_part_kernels_2(kind, &A, &k); break;
+        case 3: rac_part_kernels_3(kind, &A, &k); break;
+        case 4: rac_part_kernels_4(kind, &A, &k); break;
+        default: rac_part_kernels_8(kind, &A, &k); break;
     }
-}
-
-// (groups spanning chunks, GQ = 7, exceed the 256 channels of per-group
-// outliers, so that form has no mode 2)
-template <int GA, int GQ>
-Kernels encode_for(int bits, int om) {
-    if constexpr (GQ != 7) {
-        if (om == 2) return encode_for_bits<GA, GQ, 2>(bits);
-    }
-    return om == 1 ? encode_for_bits<GA, GQ, 1>(bits) : encode_for_bits<GA, GQ, 0>(bits);
-}
-
-int outlier_mode(const Args& A) { return A.gout ? 2 : (A.k > 0 ? 1 : 0); }
-
-// Specialized group shapes: 64/64, 128/128, the mixed 64/128 and 128/64, and
-// 128 with one scale per row of up to 8192 channels; anything else takes the
-// generic kernel, whose wavefronts meet where a group spans chunks.
-Kernels pick_encode(const Args& A, int bits) {
-    const int ga = A.lg_cpg_a > 0 ? 7 : A.lane_lv_a;
-    const int gq = A.lg_cpg_q > 0 ? 7 : A.lane_lv_q;
-    const int om = outlier_mode(A);
-    if (ga == 3 && gq == 3) return encode_for<3, 3>(bits, om);
-    if (ga == 4 && gq == 4) return encode_for<4, 4>(bits, om);
-    if (ga == 3 && gq == 4) return encode_for<3, 4>(bits, om);
-    if (ga == 4 && gq == 3) return encode_for<4, 3>(bits, om);
-    if (ga == 4 && gq == 7) return encode_for<4, 7>(bits, om);
-    Kernels k = encode_for<-1, -1>(bits, om);
-    if (ga == 7 || gq == 7) k.one = nullptr;
     return k;
-}
-
-// The rows kernel in its two launch shapes: workgroups that take rows in
-// strides of the grid, and one workgroup per row (null with given pairs, whose
-// search for the row's segment the strided form overlaps with the row before:
-// 4096 x 4096 pooled 43.5 us strided, 47.0 with one workgroup per row).
-template <int BITS, int GA, int GQ, int CPW, bool GIVEN, bool TWO, bool BIG>
-Kernels rows_pair() {
-    if constexpr (GIVEN)
-        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, true, TWO, BIG>, nullptr, false};
-    else
-        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG>,
-                rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG, true>, false};
-}
-
-template <int GA, int GQ, int CPW, bool GIVEN, bool TWO, bool BIG>
-Kernels rows_for_bits(int bits) {
-    switch (bits) {
-        case 2: return rows_pair<2, GA, GQ, CPW, GIVEN, TWO, BIG>();
-        case 3: return rows_pair<3, GA, GQ, CPW, GIVEN, TWO, BIG>();
-        case 4: return rows_pair<4, GA, GQ, CPW, GIVEN, TWO, BIG>();
-        default: return rows_pair<8, GA, GQ, CPW, GIVEN, TWO, BIG>();
-    }
-}
-
-template <int GA, int GQ, int CPW, bool GIVEN>
-Kernels rows_for_cpw(int bits, int k) {
-    if constexpr (GIVEN) {
-        return rows_for_bits<GA, GQ, CPW, true, false, false>(bits);
-    } else {
-        if (k > kTop2) return rows_for_bits<GA, GQ, CPW, false, false, true>(bits);
-        if (k > kTop1) return rows_for_bits<GA, GQ, CPW, false, true, false>(bits);
-        return rows_for_bits<GA, GQ, CPW, false, false, false>(bits);
-    }
-}
-
-// Rows of up to 4096 channels: two chunks per wavefront; up to 8192: four.
-// The two-value threshold for kTop1 < k <= kTop2, and with the larger
-// candidate list beyond (not with given pairs, which keep the one-value
-// bound and the smaller list: every bound and list size is exact).
-template <int GA, int GQ, bool GIVEN = false>
-Kernels rows_for(int bits, int d, int k) {
-    if (d <= kRowsWaves * 2 * kChunk) return rows_for_cpw<GA, GQ, 2, GIVEN>(bits, k);
-    return rows_for_cpw<GA, GQ, 4, GIVEN>(bits, k);
 }
 
 // Rows with outliers take the NW-wavefront kernel when it holds the whole
@@ -2809,39 +2747,6 @@ Kernels rows_for(int bits, int d, int k) {
 // one-wavefront-per-chunk kernel).
 bool use_rows_kernel(const Args& A) {
     return outlier_mode(A) == 1 && !A.fixed && A.d <= kRowsMaxD && A.lg_cpg_a == 0 && A.lg_cpg_q == 0;
-}
-
-Kernels pick_rows(const Args& A, int bits) {
-    // given pairs (pooled fit): the fixed 128 and 64 shapes and the generic one
-    if (A.cf_given) {
-        if (A.lane_lv_a == 4 && A.lane_lv_q == 4) return rows_for<4, 4, true>(bits, A.d, A.k);
-        if (A.lane_lv_a == 3 && A.lane_lv_q == 3) return rows_for<3, 3, true>(bits, A.d, A.k);
-        return rows_for<-1, -1, true>(bits, A.d, A.k);
-    }
-    if (A.lane_lv_a == 3 && A.lane_lv_q == 3) return rows_for<3, 3>(bits, A.d, A.k);
-    if (A.lane_lv_a == 4 && A.lane_lv_q == 4) return rows_for<4, 4>(bits, A.d, A.k);
-    if (A.lane_lv_a == 3 && A.lane_lv_q == 4) return rows_for<3, 4>(bits, A.d, A.k);
-    if (A.lane_lv_a == 4 && A.lane_lv_q == 3) return rows_for<4, 3>(bits, A.d, A.k);
-    return rows_for<-1, -1>(bits, A.d, A.k);
-}
-
-template <int OM, bool BF16>
-KernelFn decode_for(int bits) {
-    switch (bits) {
-        case 2: return rac_decode_kernel<2, OM, BF16>;
-        case 3: return rac_decode_kernel<3, OM, BF16>;
-        case 4: return rac_decode_kernel<4, OM, BF16>;
-        default: return rac_decode_kernel<8, OM, BF16>;
-    }
-}
-
-KernelFn pick_decode(const Args& A, int bits) {
-    const bool bf16 = A.xhat_bf16 != 0;
-    switch (outlier_mode(A)) {
-        case 1: return bf16 ? decode_for<1, true>(bits) : decode_for<1, false>(bits);
-        case 2: return bf16 ? decode_for<2, true>(bits) : decode_for<2, false>(bits);
-        default: return bf16 ? decode_for<0, true>(bits) : decode_for<0, false>(bits);
-    }
 }
 
 // Launch facts of one kernel on one device: compute units and resident
@@ -3017,7 +2922,7 @@ rac_status run_decode(const rac_config* cfg, const void* wire, const void* ref, 
     const int strided_max = A.nch <= 2 * kRowsWaves ? kDecodeStridedRowsMax
                           : outlier_mode(A) == 2    ? kStridedRowsMax
                                                     : kWideStridedRowsMax;
-    return launch({pick_decode(A, cfg->bits), nullptr, false}, A, stream, 0, outlier_mode(A) == 1 ? per_cu : 0,
+    return launch(pick_kernels(kDecodeKernels, A, cfg->bits), A, stream, 0, outlier_mode(A) == 1 ? per_cu : 0,
                   strided_max);
 }
 
@@ -3131,8 +3036,8 @@ rac_status run_encode(const rac_config* cfg, const void* x, const void* ref, con
     A.xhat = xhat;
     A.write_header = 1;
     fill_header(A, cfg, ref == nullptr);
-    if (use_rows_kernel(A)) return launch(pick_rows(A, cfg->bits), A, stream, kRowsWaves * kWave);
-    return launch(pick_encode(A, cfg->bits), A, stream);
+    if (use_rows_kernel(A)) return launch(pick_kernels(kRowsKernels, A, cfg->bits), A, stream, kRowsWaves * kWave);
+    return launch(pick_kernels(kEncodeKernels, A, cfg->bits), A, stream);
 }
 
 }  // namespace
@@ -3209,8 +3114,8 @@ rac_status rac_encode_pooled(const rac_config* cfg, const void* x, const void* r
     A.cf_given = 1;
     A.write_header = 1;
     fill_header(A, cfg, ref == nullptr, true);
-    if (use_rows_kernel(A)) return launch(pick_rows(A, cfg->bits), A, stream, kRowsWaves * kWave);
-    return launch(pick_encode(A, cfg->bits), A, stream);
+    if (use_rows_kernel(A)) return launch(pick_kernels(kRowsKernels, A, cfg->bits), A, stream, kRowsWaves * kWave);
+    return launch(pick_kernels(kEncodeKernels, A, cfg->bits), A, stream);
 }
 
 rac_status rac_reconstruct(const rac_config* cfg, const void* wire, const void* ref,
@@ -3505,3 +3410,115 @@ const char* rac_status_string(rac_status s) {
 }
 
 }  // extern "C"
+
+#else  // RAC_PART: the kernels of one bit width
+
+template <int BITS, int GA, int GQ, int OM>
+Kernels encode_pair() {
+    if constexpr (OM != 1 && GQ != 7)
+        return {rac_encode_kernel<BITS, GA, GQ, OM>, rac_encode_kernel<BITS, GA, GQ, OM, true>, true};
+    else
+        return {rac_encode_kernel<BITS, GA, GQ, OM>, nullptr, false};
+}
+
+// (groups spanning chunks, GQ = 7, exceed the 256 channels of per-group
+// outliers, so that form has no mode 2)
+template <int BITS, int GA, int GQ>
+Kernels encode_for(int om) {
+    if constexpr (GQ != 7) {
+        if (om == 2) return encode_pair<BITS, GA, GQ, 2>();
+    }
+    return om == 1 ? encode_pair<BITS, GA, GQ, 1>() : encode_pair<BITS, GA, GQ, 0>();
+}
+
+// Specialized group shapes: 64/64, 128/128, the mixed 64/128 and 128/64, and
+// 128 with one scale per row of up to 8192 channels; anything else takes the
+// generic kernel, whose wavefronts meet where a group spans chunks.
+template <int BITS>
+Kernels pick_encode(const Args& A) {
+    const int ga = A.lg_cpg_a > 0 ? 7 : A.lane_lv_a;
+    const int gq = A.lg_cpg_q > 0 ? 7 : A.lane_lv_q;
+    const int om = outlier_mode(A);
+    if (ga == 3 && gq == 3) return encode_for<BITS, 3, 3>(om);
+    if (ga == 4 && gq == 4) return encode_for<BITS, 4, 4>(om);
+    if (ga == 3 && gq == 4) return encode_for<BITS, 3, 4>(om);
+    if (ga == 4 && gq == 3) return encode_for<BITS, 4, 3>(om);
+    if (ga == 4 && gq == 7) return encode_for<BITS, 4, 7>(om);
+    Kernels k = encode_for<BITS, -1, -1>(om);
+    if (ga == 7 || gq == 7) k.one = nullptr;
+    return k;
+}
+
+// The rows kernel in its two launch shapes: workgroups that take rows in
+// strides of the grid, and one workgroup per row (null with given pairs, whose
+// search for the row's segment the strided form overlaps with the row before:
+// 4096 x 4096 pooled 43.5 us strided, 47.0 with one workgroup per row).
+template <int BITS, int GA, int GQ, int CPW, bool GIVEN, bool TWO, bool BIG>
+Kernels rows_pair() {
+    if constexpr (GIVEN)
+        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, true, TWO, BIG>, nullptr, false};
+    else
+        return {rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG>,
+                rac_encode_rows_kernel<BITS, GA, GQ, kRowsWaves, CPW, false, TWO, BIG, true>, false};
+}
+
+template <int BITS, int GA, int GQ, int CPW, bool GIVEN>
+Kernels rows_for_cpw(int k) {
+    if constexpr (GIVEN) {
+        return rows_pair<BITS, GA, GQ, CPW, true, false, false>();
+    } else {
+        if (k > kTop2) return rows_pair<BITS, GA, GQ, CPW, false, false, true>();
+        if (k > kTop1) return rows_pair<BITS, GA, GQ, CPW, false, true, false>();
+        return rows_pair<BITS, GA, GQ, CPW, false, false, false>();
+    }
+}
+
+// Rows of up to 4096 channels: two chunks per wavefront; up to 8192: four.
+// The two-value threshold for kTop1 < k <= kTop2, and with the larger
+// candidate list beyond (not with given pairs, which keep the one-value
+// bound and the smaller list: every bound and list size is exact).
+template <int BITS, int GA, int GQ, bool GIVEN = false>
+Kernels rows_for(int d, int k) {
+    if (d <= kRowsWaves * 2 * kChunk) return rows_for_cpw<BITS, GA, GQ, 2, GIVEN>(k);
+    return rows_for_cpw<BITS, GA, GQ, 4, GIVEN>(k);
+}
+
+template <int BITS>
+Kernels pick_rows(const Args& A) {
+    // given pairs (pooled fit): the fixed 128 and 64 shapes and the generic one
+    if (A.cf_given) {
+        if (A.lane_lv_a == 4 && A.lane_lv_q == 4) return rows_for<BITS, 4, 4, true>(A.d, A.k);
+        if (A.lane_lv_a == 3 && A.lane_lv_q == 3) return rows_for<BITS, 3, 3, true>(A.d, A.k);
+        return rows_for<BITS, -1, -1, true>(A.d, A.k);
+    }
+    if (A.lane_lv_a == 3 && A.lane_lv_q == 3) return rows_for<BITS, 3, 3>(A.d, A.k);
+    if (A.lane_lv_a == 4 && A.lane_lv_q == 4) return rows_for<BITS, 4, 4>(A.d, A.k);
+    if (A.lane_lv_a == 3 && A.lane_lv_q == 4) return rows_for<BITS, 3, 4>(A.d, A.k);
+    if (A.lane_lv_a == 4 && A.lane_lv_q == 3) return rows_for<BITS, 4, 3>(A.d, A.k);
+    return rows_for<BITS, -1, -1>(A.d, A.k);
+}
+
+template <int BITS>
+Kernels pick_decode(const Args& A) {
+    const bool bf16 = A.xhat_bf16 != 0;
+    switch (outlier_mode(A)) {
+        case 1: return {bf16 ? rac_decode_kernel<BITS, 1, true> : rac_decode_kernel<BITS, 1, false>, nullptr, false};
+        case 2: return {bf16 ? rac_decode_kernel<BITS, 2, true> : rac_decode_kernel<BITS, 2, false>, nullptr, false};
+        default: return {bf16 ? rac_decode_kernel<BITS, 0, true> : rac_decode_kernel<BITS, 0, false>, nullptr, false};
+    }
+}
+
+}  // namespace
+
+#define RAC_PART_OF(bits) RAC_PART_FN(bits)
+RAC_PART_OF(RAC_PART) {
+    const Args& A = *static_cast<const Args*>(args);
+    Kernels& k = *static_cast<Kernels*>(out);
+    switch (kind) {
+        case kEncodeKernels: k = pick_encode<RAC_PART>(A); break;
+        case kRowsKernels: k = pick_rows<RAC_PART>(A); break;
+        default: k = pick_decode<RAC_PART>(A); break;
+    }
+}
+
+#endif  // RAC_PART
