@@ -402,7 +402,7 @@ size_t rac_predictor_workspace_bytes(const rac_predictor_config* cfg);
  *   h_prev    : DEVICE bf16 [batch][hidden], the previous reconstructions
  *   ref_out   : DEVICE bf16 [batch][hidden], the predicted references
  *   workspace : DEVICE scratch of rac_predictor_workspace_bytes(), 256-byte aligned
- * Argument errors are returned before any launch.  Seven kernel launches on
+ * Argument errors are returned before any launch.  Seven to ten kernel launches on
  * `stream`. */
 rac_status rac_predictor_step(const rac_predictor_config* cfg, const void* weights, void* cache, const int32_t* pos,
                               int32_t batch, const void* h_prev, void* ref_out, void* workspace,

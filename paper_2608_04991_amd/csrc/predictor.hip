@@ -24,7 +24,8 @@
 // launches of a few microseconds each.  So each product is one launch that
 // sums its whole K inside a workgroup, folds in the residual, and leaves the
 // sums of squares from which the next product forms its own RMSNorm: seven
-// launches a step whatever the batch, six products and the attention.
+// launches a step, six products and the attention (and up to three more where
+// products are so large that their rows are normalized once, ahead of them).
 #include <hip/hip_runtime.h>
 
 #include <stddef.h>
@@ -70,7 +71,8 @@ __device__ __forceinline__ uint16_t to_bf(float v) {  // round to nearest even (
 // the residual stream and its RMSNorm need no launch of their own: the product
 // that forms h (kHidden) adds the residual, stores h and the sum of squares of
 // every (row, COLS columns); the product that consumes it (NORM) sums those of
-// its rows and forms bf16(h / sqrt(mean(h^2) + eps) * gain) on the way to LDS.
+// its rows and forms bf16(h / sqrt(mean(h^2) + eps) * gain) on the way to LDS
+// (the largest products read it from a launch of its own, see prod_wide).
 enum Epi { kHidden, kQkv, kGate, kOut };
 
 struct Prod {
@@ -316,6 +318,44 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
             const float g0 = v[0] / (1.0f + __expf(-v[0])) * v[1];
             const float g1 = v[2] / (1.0f + __expf(-v[2])) * v[3];
             if (in) *reinterpret_cast<uint32_t*>(p.out16 + (size_t)row * (p.N / 2) + col / 2) = pack2(g0, g1);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The normalized activations of one batch row per workgroup, as the products
+// form them while loading (see prod_wide for when this launch pays for itself).
+constexpr int kNormThreads = 256;
+
+__global__ __launch_bounds__(kNormThreads) void pred_norm(Prod p, uint16_t* n) {
+    const int row = blockIdx.x, t = threadIdx.x;
+    const float* const h = p.h + (size_t)row * p.K;
+    const float* const ss = p.ssin + (size_t)row * p.nss;
+    // (channels 4 t .. 4 t + 3 and, beyond 1024, 1024 + 4 t ..)
+    f32x4 hv[2];
+    u32x2 gv[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int c = 4 * (t + kNormThreads * i);
+        if (c < p.K) {
+            hv[i] = *reinterpret_cast<const f32x4*>(h + c);
+            gv[i] = *reinterpret_cast<const u32x2*>(p.gain + c);
+        }
+    }
+    // every wavefront sums the row's sums of squares (at most 256)
+    const int lane = t & (kW - 1);
+    float q = 0.0f;
+    for (int i = lane; i < p.nss; i += kW) q = q + ss[i];
+    for (int o = 1; o < kW; o <<= 1) q = q + __shfl_xor(q, o);
+    const float inv = 1.0f / __builtin_sqrtf(q / (float)p.K + kEps);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int c = 4 * (t + kNormThreads * i);
+        if (c < p.K) {
+            const float g0 = __uint_as_float(gv[i][0] << 16), g1 = __uint_as_float(gv[i][0] & 0xFFFF0000u);
+            const float g2 = __uint_as_float(gv[i][1] << 16), g3 = __uint_as_float(gv[i][1] & 0xFFFF0000u);
+            *reinterpret_cast<u32x2*>(n + (size_t)row * p.K + c) =
+                u32x2{pack2(hv[i][0] * inv * g0, hv[i][1] * inv * g1), pack2(hv[i][2] * inv * g2, hv[i][3] * inv * g3)};
         }
     }
 }
@@ -567,9 +607,9 @@ PLayout playout(const rac_predictor_config* c) {
 
 // The total is part of the interface (callers size the scratch by it, and a
 // smaller one is refused), so it stays what it was when the products left
-// partial sums and the normalized rows in memory: the `spare` bytes.
+// partial sums in memory, where `ss` now is.
 struct PWork {
-    uint64_t ss, h0, h1, h2, spare, qkv, o, gg, total;
+    uint64_t ss, h0, h1, h2, n, qkv, o, gg, total;
 };
 
 PWork pwork(const rac_predictor_config* c, int B) {
@@ -582,7 +622,7 @@ PWork pwork(const rac_predictor_config* c, int B) {
     W.h0 = take((uint64_t)B * m * 4);
     W.h1 = take((uint64_t)B * m * 4);
     W.h2 = take((uint64_t)B * m * 4);
-    W.spare = take((uint64_t)B * m * 2);
+    W.n = take((uint64_t)B * m * 2);
     W.qkv = take((uint64_t)B * 3 * m * 4);
     W.o = take((uint64_t)B * m * 2);
     W.gg = take((uint64_t)B * f * 2);
@@ -618,21 +658,44 @@ int64_t tiles(const Prod& p, int tm, int tn) {
 // smallest tiles leave half the chip idle: then eight columns a workgroup
 // (half of the matrix core's tile unused) on twice the workgroups.  us, 16
 // columns and 8: 1 x 512 of K = 4096: 4.6, 4.0; 64 x 512 of 4096 (128 tiles):
-// 5.3, 4.9; 128 x 512 of 4096 (256 tiles): 5.5, 7.1.
+// 5.3, 4.9; 128 x 512 of 4096 (256 tiles): 5.5, 7.1.  (2, 4) against (2, 2):
+// 143 x 2048 of 8192 (160 tiles) 20.6, 25.4; 256 x 1536 of 3072 9.8, 13.4; 143 x
+// 1536 of 3072 (120 tiles) 9.7, 7.8.
 rac_status prod_hidden(Prod& p, hipStream_t st) {
     p.nss = p.N / 16;
     if (tiles(p, 1, 1) <= 128) {
         p.nss = p.N / 8;
         return prod_launch<1, 1, 8, 2, kHidden, false, 8>(p, st);
     }
+    if (p.M > 16 && tiles(p, 2, 4) >= 160) return prod_launch<2, 4, 8, 1, kHidden, false>(p, st);
     if (p.M > 16 && tiles(p, 2, 2) >= kFill) return prod_launch<2, 2, 8, 2, kHidden, false>(p, st);
     if (tiles(p, 1, 2) >= kFill) return prod_launch<1, 2, 8, 2, kHidden, false>(p, st);
     return prod_launch<1, 1, 8, 2, kHidden, false>(p, st);
 }
 
-// Products from the normalized model width (many columns, short K).
+// Products from the normalized model width (many columns, short K).  A tile
+// that normalizes its own rows reads them in fp32 and converts them once per
+// column tile; from 9e8 multiply-adds on a launch that writes them as bf16
+// first (3 us) saves more than it costs.  us, normalizing and reading bf16:
+// 64 x 4096 of K = 512 4.6, 3.5; 256 x 4096 of 512 (5e8) 7.9, 5.6; 64 x 8192 of
+// 1024 (5e8) 8.6, 5.6; 256 x 3072 of 1024 (8e8) 10.6, 7.3; 256 x 8192 of 1024
+// 21.9, 11.9; 256 x 16384 of 2048 79, 41.
+// With bf16 rows the (4, 4) tile is faster where the batch fills its 64 rows
+// or K is long: 256 x 8192 of 1024 11.9, (2, 4) 13.4; 96 x 9216 of 1536 12.9,
+// 10.3; 143 x 16384 of 2048 30, 39.
 template <int EPI>
-rac_status prod_wide(const Prod& p, hipStream_t st) {
+rac_status prod_wide(const Prod& p, uint16_t* n, hipStream_t st) {
+    if ((int64_t)p.M * p.N * p.K >= 900000000) {
+        Prod b = p;
+        void* args[] = {&b, &n};
+        if (hipLaunchKernel(reinterpret_cast<const void*>(pred_norm), dim3((unsigned)p.M), dim3(kNormThreads), args, 0,
+                            st) != hipSuccess)
+            return RAC_ERR_HIP;
+        b.a = n;
+        const int pad = (p.M + 63) / 64 * 64;
+        if (p.K >= 2048 || 4 * pad <= 5 * p.M) return prod_launch<4, 4, 4, 1, EPI, false>(b, st);
+        return prod_launch<2, 4, 4, 1, EPI, false>(b, st);
+    }
     if (p.M > 16 && tiles(p, 2, 4) >= kFill) return prod_launch<2, 4, 4, 1, EPI, true>(p, st);
     if (tiles(p, 1, 4) >= kFill) return prod_launch<1, 4, 4, 2, EPI, true>(p, st);
     if (tiles(p, 1, 2) >= kFill) return prod_launch<1, 2, 4, 2, EPI, true>(p, st);
@@ -712,6 +775,7 @@ rac_status rac_predictor_step(const rac_predictor_config* cfg, const void* weigh
     float* h1 = reinterpret_cast<float*>(ws + Wb.h1);
     float* h2 = reinterpret_cast<float*>(ws + Wb.h2);
     float* qkv = reinterpret_cast<float*>(ws + Wb.qkv);
+    uint16_t* n = reinterpret_cast<uint16_t*>(ws + Wb.n);
     uint16_t* o = reinterpret_cast<uint16_t*>(ws + Wb.o);
     uint16_t* gg = reinterpret_cast<uint16_t*>(ws + Wb.gg);
     const uint16_t* x = static_cast<const uint16_t*>(h_prev);
@@ -724,20 +788,20 @@ rac_status rac_predictor_step(const rac_predictor_config* cfg, const void* weigh
     if ((s = prod_hidden(p, st)) != RAC_OK) return s;
     // q, k, v; attention over the window
     p.h = h0; p.ssin = ss; p.gain = wt(L.g1); p.w = wt(L.w_qkv); p.N = 3 * m; p.K = m; p.out = qkv;
-    if ((s = prod_wide<kQkv>(p, st)) != RAC_OK) return s;
+    if ((s = prod_wide<kQkv>(p, n, st)) != RAC_OK) return s;
     if ((s = attention(cfg, qkv, cache, pos, B, o, st)) != RAC_OK) return s;
     // h1 = h0 + o W_o^T
     p.a = o; p.w = wt(L.w_o); p.N = m; p.K = m; p.resid = h0; p.out = h1;
     if ((s = prod_hidden(p, st)) != RAC_OK) return s;
     // SwiGLU; h2 = h1 + g W_down^T
     p.h = h1; p.gain = wt(L.g2); p.w = wt(L.w_gu); p.N = 2 * f; p.K = m; p.out16 = gg;
-    if ((s = prod_wide<kGate>(p, st)) != RAC_OK) return s;
+    if ((s = prod_wide<kGate>(p, n, st)) != RAC_OK) return s;
     p.a = gg; p.w = wt(L.w_down); p.N = m; p.K = f; p.resid = h1; p.out = h2;
     if ((s = prod_hidden(p, st)) != RAC_OK) return s;
     // R = x + n3 W_out^T (bf16)
     p.h = h2; p.gain = wt(L.g3); p.w = wt(L.w_out); p.N = d; p.K = m; p.resid16 = x;
     p.out16 = static_cast<uint16_t*>(ref_out);
-    return prod_wide<kOut>(p, st);
+    return prod_wide<kOut>(p, n, st);
 }
 
 }  // extern "C"

@@ -124,11 +124,13 @@ def test_predictor_small_batches_fold_the_norms(hidden, model, heads, ffn, windo
 
 
 @pytest.mark.parametrize("hidden,model,heads,ffn,window,batch", [
-    (512, 2048, 32, 256, 3, 33), (8192, 128, 2, 8192, 5, 1), (512, 2048, 32, 128, 2, 130)])
+    (512, 2048, 32, 256, 3, 33), (8192, 128, 2, 8192, 5, 1), (512, 2048, 32, 128, 2, 130),
+    (8192, 1536, 24, 8192, 3, 75), (2048, 2048, 32, 4096, 2, 60)])
 def test_predictor_product_tiles(hidden, model, heads, ffn, window, batch):
     # every tile of the products with a ragged last row tile (33 = 2 x 16 + 1
     # and 32 + 1; 130 = 4 x 32 + 2; 1), and K shares from none at all (two
-    # units of 64 channels over eight wavefronts) to sixteen units
+    # units of 64 channels over eight wavefronts) to sixteen units; the last
+    # three also take products whose rows are normalized ahead of them
     cfg = rac.PredictorConfig(hidden, model, heads, ffn, window, batch)
     say(f"[gpu] predictor {hidden}/{model}/{heads}/{ffn}, window {window}, batch {batch}, 3 steps")
     _run(cfg, batch, 3, lambda s, b: s + b % 4, seed=5)
