@@ -6,20 +6,20 @@
 // entry point is documented in include/rac.h.
 //
 // Mapping onto CDNA4.  The codec is a per-token-row stream with no dense
-// contraction, so it is HBM-bound and uses no MFMA.  One workgroup owns one
-// token row and one 64-lane wavefront owns one 512-channel chunk of it: lane l
-// of wave w holds channels [512w + 8l, 512w + 8l + 8), one 128-bit load of x
-// and one of ref per lane, fully coalesced.  Each lane keeps its 8 channels in
-// registers through fit, residual, outlier choice, scale, quantization,
-// packing and the fused sender reconstruction, so every byte of x/ref is read
-// from HBM once and every output byte written once.  Work that spans chunks
-// (the per-token outlier choice, groups wider than 512 channels) goes through
-// LDS with workgroup barriers; everything else is wave-local.  (The
-// per-token outlier encode deals a row's chunks round four wavefronts, two or
-// four chunks each.)  Up to a few rows per resident workgroup the grid is the
-// resident workgroups, taking rows in strides with the next row prefetched;
-// beyond that, one workgroup per row, which keeps the rows in flight close
-// together in memory.
+// contraction, so it is HBM-bound and uses no MFMA.  One 64-lane wavefront
+// owns one 512-channel chunk of one token row: lane l of chunk w holds channels
+// [512w + 8l, 512w + 8l + 8), one 128-bit load of x and one of ref per lane,
+// fully coalesced.  Each lane keeps its 8 channels in registers through fit,
+// residual, outlier choice, scale, quantization, packing and the fused sender
+// reconstruction, so every byte of x/ref is read from HBM once and every output
+// byte written once.  Where the chunks of a row never meet (no outliers or
+// per-group ones, groups inside a chunk) the wavefronts are handed out as
+// (row, chunk) pairs; work that spans chunks (the per-token outlier choice,
+// groups wider than 512 channels) goes through LDS with workgroup barriers, and
+// a row is one workgroup.  (The per-token outlier encode deals a row's chunks
+// round four wavefronts, two or four chunks each.)  Rows are taken in order,
+// which keeps the rows in flight close together in memory, or in strides of a
+// resident grid with the next row prefetched (see launch).
 //
 // Exactness.  The sums of the fit follow a fixed pairwise tree over channel
 // order: a lane-local tree over its 8 contiguous channels, a butterfly across
@@ -1332,7 +1332,8 @@ void rac_encode_kernel(Args A) {
 // registers and their E in LDS, where the chunk's reconstruction is later
 // staged for the store.  Keeping E out of registers leaves room to prefetch
 // the next row (x once the fit is done, each ref chunk once its R~ is
-// formed) at seven (CPW = 2) or five (CPW = 4) wavefronts per SIMD.  The
+// formed) at seven (CPW = 2) or five (CPW = 4) wavefronts per SIMD; with one
+// workgroup per row (ONE) R~ takes the place of both, at eight.  The
 // per-token outlier choice costs
 // two barriers between NW wavefronts, and its threshold search and ranking
 // run NW times per row instead of once per chunk.
