@@ -56,7 +56,6 @@ constexpr int kFlatWaves = 4;      // wavefronts per workgroup where each takes 
 // workgroup per row
 constexpr int kStridedRowsMax = 6;
 constexpr int kWideStridedRowsMax = 4;
-constexpr int kDecodeStridedRowsMax = 3;
 constexpr int kManyRows = 8192;
 constexpr size_t kSevenPerCu = 2560;  // LDS bytes that keep an eighth workgroup off a compute unit
 constexpr uint32_t kMaxDispatchItems = 0xFFFFFFFFu;  // work-items one dispatch holds (per dimension)
@@ -2822,15 +2821,18 @@ rac_status device_cus(int* cus) {
 //     workgroups a compute unit instead of eight, by LDS that is requested and
 //     not used: 65536 x 3584 339.8 against 350.6 us, 32768 x 4096 194.8
 //     against 197.5 (32768 x 2048, which stays at eight, 109.2 against 107.1).
-//   - The decode: strided up to kDecodeStridedRowsMax; beyond 4096 channels
-//     up to kWideStridedRowsMax, with per-group outliers kStridedRowsMax.  us,
-//     strided and one per row: 3072 x 4096 16.9 and 16.8, 4096 x 4096 21.3 and
-//     20.8, 8192 x 4096 40.5 and 37.4, 2048 x 8192 21.1 and 21.2, 3072 x 8192
-//     30.9 and 29.5, with k_g = 2 31.2 and 34.5.
+//   - The decode: strided up to kStridedRowsMax.  At three to six rows a
+//     resident workgroup, one per row is a few percent faster where the fp32
+//     output and a reference make the call a stream (4916 x 3072 20.6 us
+//     strided, 19.2 one per row; 5258 x 3840 27.9, 25.9) and far slower
+//     elsewhere (bf16 output: 3604 x 3648 with k_g = 2 14.6, 17.6, 2855 x 7936
+//     11.2, 17.2; 2052 x 7424 with k = 16 11.8, 18.0).
 //   - The other kernels (a row's wavefronts meet, one form): strided up to
 //     kStridedRowsMax.
-rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0, int max_per_cu = 0,
-                  int strided_max = kStridedRowsMax) {
+// The rows a resident workgroup takes are counted on the occupancy itself: a
+// grid cut to max_per_cu gives each of its workgroups more (the per-token
+// decode up to twice as many).
+rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0, int max_per_cu = 0) {
     KernelFn fn = k.fn;
     const int64_t rows = A.tokens;
     // kernels launched with one wavefront per chunk stage through a
@@ -2839,6 +2841,7 @@ rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0,
     if (staged) threads = A.nch * kWave;
     size_t lds = staged ? (size_t)A.nch * kSlice * sizeof(float4) : 0;
     int64_t blocks = rows <= 0 ? 1 : rows;
+    int strided_max = kStridedRowsMax;
     if (k.one) strided_max = !k.flat && A.nch > 2 * kRowsWaves ? kWideStridedRowsMax : 0;
     if (rows > 256 && A.launch_shape != 2 && (strided_max > 0 || A.launch_shape == 1)) {
         int cus = 0, per_cu = 0;
@@ -2920,11 +2923,7 @@ rac_status run_decode(const rac_config* cfg, const void* wire, const void* ref, 
     // workgroups, each taking more rows, measured fastest: 4-8% below a full
     // grid at 4096 x 4096 and 16384 x 3584)
     const int per_cu = A.nch <= 8 ? 16 / A.nch : 2;
-    const int strided_max = A.nch <= 2 * kRowsWaves ? kDecodeStridedRowsMax
-                          : outlier_mode(A) == 2    ? kStridedRowsMax
-                                                    : kWideStridedRowsMax;
-    return launch(pick_kernels(kDecodeKernels, A, cfg->bits), A, stream, 0, outlier_mode(A) == 1 ? per_cu : 0,
-                  strided_max);
+    return launch(pick_kernels(kDecodeKernels, A, cfg->bits), A, stream, 0, outlier_mode(A) == 1 ? per_cu : 0);
 }
 
 }  // namespace

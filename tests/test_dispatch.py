@@ -1,0 +1,40 @@
+"""The kernels and grids that calls launch, as the library itself decides them
+(tests/dispatch.py records them without a GPU, on a device of 256 compute units
+of 32 wavefronts), where a wrong decision changes no result but its time."""
+from __future__ import annotations
+
+import os
+
+import pytest
+
+import paper_2608_04991_amd as rac
+from tests.dispatch import launches
+
+GRP = rac.RAC_FLAG_GROUP_OUTLIERS
+BF16 = rac.RAC_FLAG_XHAT_BF16
+FIX = rac.RAC_FLAG_FIXED_STEP
+STRIDED = rac.RAC_FLAG_LAUNCH_STRIDED
+PER_ROW = rac.RAC_FLAG_LAUNCH_PER_ROW
+CUS, WAVES = 256, 32  # the recorded device
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    if not os.path.exists(rac.library_path()):
+        pytest.fail("librac.so is not built; run __graft_entry__.build()")
+    tmp = tmp_path_factory.mktemp("recorder")
+    return lambda calls: launches(calls, tmp)
+
+
+@pytest.mark.parametrize("d", [1024, 3648, 4096, 5120, 7936, 8192])
+@pytest.mark.parametrize("k,flags", [(0, 0), (0, BF16), (2, GRP), (8, 0), (4, FIX)])
+def test_decode_strides_over_up_to_six_rows_a_resident_workgroup(record, d, k, flags):
+    nch = -(-d // 512)
+    fits = CUS * (WAVES // nch)
+    rows = (256, 257, fits, fits + 1, 6 * fits, 6 * fits + 1)
+    got = record([("decode", [T, d, 64, 64, 4, k, flags]) for T in rows])
+    # per-token outliers: 16 wavefronts a compute unit, at least two workgroups
+    grid = CUS * (max(2, 16 // nch) if k and not flags & GRP else WAVES // nch)
+    want = [256, min(257, grid), grid, grid, grid, 6 * fits + 1]
+    assert [l.grid for (l,) in got] == want
+    assert all(l.threads == 64 * nch and l.kernel.startswith("rac_decode_kernel<4, ") for (l,) in got)
