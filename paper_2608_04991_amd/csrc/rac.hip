@@ -297,6 +297,41 @@ __device__ __forceinline__ void quantize8(float* ed, uint32_t sh, float s, bool 
     }
 }
 
+// The same codes from the clamped product, each step rounded by itself, as the
+// chunk kernel with per-token outliers forms them.  With quantize8 its register
+// counts fall on the other side of an occupancy step: 106 instead of 96 at 4
+// bits and fixed group shapes (four wavefronts a SIMD instead of five: 4962 x
+// 2432 with k = 8 66.2 us, 39.8 clamped), and 96 instead of 100 with other
+// shapes (five instead of four, with which the workgroups of a small call share
+// compute units while others idle: 727 x 4864 with k = 32 44.4, 35.4); at equal
+// occupancy it is about 1% slower.  1/s is within 2^-23 of its value, the product
+// and E/s each within 2^-24 of theirs, so for |t| <= 128 the fast rounding is
+// exact outside 2^-15 of a tie.
+template <int BITS>
+__device__ __forceinline__ void quantize8_clamped(const float* ed, uint32_t sh, float s, float* mg, float* qf) {
+    constexpr float q = (float)((1 << (BITS - 1)) - 1);
+    constexpr float kNear = 0.5f - 0x1p-14f;
+    const float inv = sh ? __builtin_amdgcn_rcpf(s) : 0.0f;
+    float tc[8];
+    float dist = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        tc[j] = __builtin_amdgcn_fmed3f(ed[j] * inv, -q, q);
+        mg[j] = tc[j] + kMagic;
+        qf[j] = mg[j] - kMagic;
+        dist = __builtin_fmaxf(dist, __builtin_fabsf(tc[j] - qf[j]));
+    }
+    if (dist > kNear) {  // some quotient is near a tie: use the exact one
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (__builtin_fabsf(tc[j] - qf[j]) > kNear) {
+                tc[j] = __builtin_amdgcn_fmed3f(ed[j] / s, -q, q);
+                mg[j] = tc[j] + kMagic;
+                qf[j] = mg[j] - kMagic;
+            }
+    }
+}
+
 // Closed-form least squares of one group from its centred moments:
 // alpha* = C_rx / C_rr, beta* = m_x - alpha* m_r; a zero-variance reference
 // gives (0, m_x).  Returns the fp16 pair (alpha | beta << 16), each the IEEE
@@ -1131,9 +1166,13 @@ __device__ __forceinline__ uint32_t select_outliers(const Args& A, RowShared& S,
 // workgroup: rows of many chunks then leave no wavefront slots empty between
 // workgroups (at 80 registers a compute unit holds one 16-wavefront row of
 // 8192 channels, two thirds of its slots).
+// (Per-token outliers at 4 bits and fixed group shapes: asked to, the compiler
+// fits 96 registers, five wavefronts a SIMD, instead of 97; the other widths
+// take 101 to 106 and gain on large calls what they lose on small ones, whose
+// workgroups then share compute units while others idle.)
 template <int BITS, int GA, int GQ, int OM, bool FLAT = false>
 __global__ __launch_bounds__(FLAT ? kWave * kFlatWaves : kWave * kMaxWaves)
-__attribute__((amdgpu_waves_per_eu(OM == 2 && GQ >= 0 ? (FLAT ? 7 : 6) : 1)))
+__attribute__((amdgpu_waves_per_eu(OM == 2 && GQ >= 0 ? (FLAT ? 7 : 6) : OM == 1 && BITS == 4 && GQ >= 0 && GQ < 7 ? 5 : 1)))
 void rac_encode_kernel(Args A) {
     // LDS state of a row, double-buffered by row parity: every row that uses
     // LDS has a workgroup barrier, so no wave is more than one row ahead.
@@ -1309,7 +1348,10 @@ void rac_encode_kernel(Args A) {
 
         // a6-a8: quantize (round half to even), pack, reconstruct
         float mg[8], qf[8];
-        quantize8<BITS>(ed, sh, s, A.fixed != 0, mg, qf);
+        if constexpr (OM == 1)
+            quantize8_clamped<BITS>(ed, sh, s, mg, qf);
+        else
+            quantize8<BITS>(ed, sh, s, A.fixed != 0, mg, qf);
         Packed<BITS> pk{};
         float H[8];
 #pragma unroll
