@@ -125,8 +125,10 @@ enum {
      * the device holds at once, each taking rows in strides with its next row
      * prefetched, while that gives each only a few (four to six; twice that in
      * the per-token decode, which holds half the workgroups) rows: over many
-     * rows the strided workgroups drift apart and the HBM writes lose locality.  STRIDED always takes the strided
-     * grid, PER_ROW always rows in order; setting both is RAC_ERR_INVALID. */
+     * rows the strided workgroups drift apart and the HBM writes lose locality.  STRIDED always takes the kernels
+     * of the strided grid (with a row for each workgroup where the device
+     * holds that many), PER_ROW always rows in order; setting both is
+     * RAC_ERR_INVALID. */
     RAC_FLAG_LAUNCH_STRIDED = 1u << 3,
     RAC_FLAG_LAUNCH_PER_ROW = 1u << 4
 };

@@ -2890,13 +2890,14 @@ rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0,
     if (staged) threads = A.nch * kWave;
     size_t lds = staged ? (size_t)A.nch * kSlice * sizeof(float4) : 0;
     int64_t blocks = rows <= 0 ? 1 : rows;
+    const bool strided = A.launch_shape == 1;  // asked for: fn, also where each of its workgroups gets one row
     int strided_max = kStridedRowsMax;
     if (k.one) strided_max = !k.flat && A.nch > 2 * kRowsWaves ? kWideStridedRowsMax : 0;
-    if (rows > 256 && A.launch_shape != 2 && (strided_max > 0 || A.launch_shape == 1)) {
+    if (rows > 256 && A.launch_shape != 2 && (strided_max > 0 || strided)) {
         int cus = 0, per_cu = 0;
         if (resident(reinterpret_cast<const void*>(fn), threads, lds, &cus, &per_cu) != RAC_OK) return RAC_ERR_HIP;
         const int64_t fits = (int64_t)cus * (per_cu > 0 ? per_cu : 1);  // workgroups the device holds at once
-        if (A.launch_shape == 1 || rows <= (int64_t)strided_max * fits) {
+        if (strided || rows <= (int64_t)strided_max * fits) {
             if (max_per_cu > 0 && per_cu > max_per_cu) per_cu = max_per_cu;
             int64_t resident = (int64_t)cus * (per_cu > 0 ? per_cu : 1);
             // a gathered reference: at most kMaxGatherRows rows per workgroup,
@@ -2913,7 +2914,8 @@ rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0,
     const int64_t max_blocks = (int64_t)(kMaxDispatchItems / (uint32_t)threads);
     if (blocks > max_blocks) blocks = max_blocks;
     if (A.ref_rows && blocks * kMaxGatherRows < rows) return RAC_ERR_UNSUPPORTED;
-    if (k.one && k.flat && blocks == rows) {
+    const bool one = k.one && blocks == rows && !strided;
+    if (one && k.flat) {
         const int64_t flat = (rows * A.nch + kFlatWaves - 1) / kFlatWaves;
         if (flat <= (int64_t)(kMaxDispatchItems / (kFlatWaves * kWave))) {
             fn = k.one;
@@ -2921,7 +2923,7 @@ rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0,
             threads = kFlatWaves * kWave;
             lds = kFlatWaves * kSlice * sizeof(float4);
         }
-    } else if (k.one && blocks == rows) {
+    } else if (one) {
         fn = k.one;
         if (rows > kManyRows && A.k <= kTop1 && A.nch > kRowsWaves && A.nch <= 2 * kRowsWaves) lds = kSevenPerCu;
     }

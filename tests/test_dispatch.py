@@ -38,3 +38,21 @@ def test_decode_strides_over_up_to_six_rows_a_resident_workgroup(record, d, k, f
     want = [256, min(257, grid), grid, grid, grid, 6 * fits + 1]
     assert [l.grid for (l,) in got] == want
     assert all(l.threads == 64 * nch and l.kernel.startswith("rac_decode_kernel<4, ") for (l,) in got)
+
+
+@pytest.mark.parametrize("d,k,flags,form", [
+    (512, 0, 0, "chunks"), (4096, 2, GRP, "chunks"), (7168, 0, BF16, "chunks"), (1024, 4, 0, "rows"),
+    (4096, 17, 0, "rows"), (4096, 64, 0, "rows"), (5120, 8, 0, "rows"), (8192, 64, 0, "rows")])
+def test_strided_hint_takes_the_strided_kernel_at_any_row_count(record, d, k, flags, form):
+    # (both kernels with a form that takes one row, or one chunk, have it as
+    # their last template argument)
+    rows = [1, 256, 257, 300, 1100, 5000, 40000]
+    got = record([("encode", [T, d, 64, 64, 4, k, flags | hint]) for hint in (STRIDED, PER_ROW) for T in rows])
+    kernel = {"chunks": "rac_encode_kernel<4, 3, 3, ", "rows": "rac_encode_rows_kernel<4, 3, 3, "}[form]
+    strided, per_row = got[:len(rows)], got[len(rows):]
+    fits = CUS * (WAVES // (4 if form == "rows" else -(-d // 512)))
+    for T, (l,) in zip(rows, strided):
+        assert l.kernel.startswith(kernel) and l.kernel.endswith(", false>") and l.grid == min(T, fits)
+    for T, (l,) in zip(rows, per_row):
+        assert l.kernel.startswith(kernel) and l.kernel.endswith(", true>")
+        assert l.grid == (T if form == "rows" else -(-T * -(-d // 512) // 4))

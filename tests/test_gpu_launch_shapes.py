@@ -229,3 +229,33 @@ def test_flat_and_strided_forms_of_the_chunk_kernel(T, d, ga, gq, bits, k):
             torch.cuda.synchronize()
             assert np.array_equal(wire.cpu().numpy(), _bytes(gw).ravel())
             assert np.array_equal(_bytes(xh.cpu().numpy()), _bytes(gx))
+
+
+@pytest.mark.parametrize("T,d,ga,gq,bits,k,flags", [
+    (2900, 4608, 128, 128, 4, 8, 0), (2700, 8192, 64, 64, 3, 16, 0), (2700, 8192, 128, 64, 8, 48, 0),  # four chunks a
+    (2700, 7680, 64, 128, 2, 64, 0), (2700, 8192, 256, 256, 4, 17, 0),                                # wavefront
+    (3900, 1024, 128, 128, 4, 48, 0), (3900, 2048, 32, 32, 2, 17, 0), (4100, 520, 8, 8, 3, 64, 0),     # two
+    (4700, 2048, 128, 128, 4, 2, GRP), (4700, 2560, 64, 64, 8, 0, rac.RAC_FLAG_XHAT_BF16)])            # (row, chunk) forms
+def test_strided_form_takes_several_rows(T, d, ga, gq, bits, k, flags):
+    # more rows than two rounds of resident workgroups, so that the strided
+    # kernels work on prefetched rows; tied, zero-residual and ordinary rows
+    # side by side.  Rows are coded independently, so the oracle codes a sample
+    # of them: the ends, every multiple of 256 and its neighbours
+    rng = np.random.default_rng([d, k, T])
+    xb, rb, _ = wl.prefill_uplink(13, tokens=T, hidden=d) if d % 128 == 0 else \
+        wl.affine_pair(wl.AffineRecipe(T, d, 8), 13)
+    xb, rb = xb.copy(), rb.copy()
+    xb[0::3] = wl.f32_to_bf16_bits(rng.choice([-1.5, 1.5], size=xb[0::3].shape).astype(np.float32))
+    rb[0::3] = 0
+    xb[1::30] = rb[1::30]
+    c = cfgd(T, d, ga, gq, bits, k, flags)
+    rows = np.unique(np.clip(np.concatenate([np.arange(0, T, 256) + o for o in (-1, 0, 1)] + [[T - 1]]), 0, T - 1))
+    outs = []
+    for hint in HINTS:
+        say(f"[gpu] strided over several rows {T}x{d} g={ga}/{gq} b={bits} k={k} flags={flags}: hint {hint}")
+        outs.append(gpu_run(dict(c, flags=flags | hint), xb, rb, None))
+    for o in outs[1:]:
+        for a, b in zip(outs[0], o):
+            assert np.array_equal(_bytes(a), _bytes(b))
+    ow, ox = oracle_run(dict(c, tokens=rows.size), xb[rows], rb[rows], None)
+    assert_parity(c, outs[1][0], outs[1][1], ow, ox, g_rows=rows, o_rows=slice(None))
