@@ -118,16 +118,16 @@ enum {
     /* Launch hints; neither changes the wire or any result, only how rows are
      * spread over workgroups, and neither is recorded in the wire.  By default
      * an encode hands its rows out in order (a workgroup per row, or a
-     * wavefront per 512 channels of a row); a decode, an encode whose rows
-     * are wider than 4096 channels (per-token outliers) or whose groups or
-     * step table make a row's wavefronts meet, and a pooled encode with
-     * per-token outliers run more than 256 rows on a grid of the workgroups
-     * the device holds at once, each taking rows in strides with its next row
-     * prefetched, while that gives each only a few (four to six; twice that in
-     * the per-token decode, which holds half the workgroups) rows: over many
-     * rows the strided workgroups drift apart and the HBM writes lose locality.  STRIDED always takes the kernels
-     * of the strided grid (with a row for each workgroup where the device
-     * holds that many), PER_ROW always rows in order; setting both is
+     * wavefront per 512 channels of a row); a decode, a pooled encode, and an
+     * encode whose rows are wider than 4096 channels (per-token outliers) or
+     * whose groups or step table make a row's wavefronts meet, run more than
+     * 256 rows on a grid of the workgroups the device holds at once, each
+     * taking rows in strides with its next row prefetched, while that gives
+     * each only a few (three to six; twice that in the per-token decode, which
+     * holds half the workgroups) rows: over many rows the strided workgroups
+     * drift apart and the HBM writes lose locality.  STRIDED always takes the
+     * kernels of the strided grid (with a row for each workgroup where the
+     * device holds that many), PER_ROW always rows in order; setting both is
      * RAC_ERR_INVALID. */
     RAC_FLAG_LAUNCH_STRIDED = 1u << 3,
     RAC_FLAG_LAUNCH_PER_ROW = 1u << 4

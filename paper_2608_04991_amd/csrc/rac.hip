@@ -56,6 +56,7 @@ constexpr int kFlatWaves = 4;      // wavefronts per workgroup where each takes 
 // workgroup per row
 constexpr int kStridedRowsMax = 6;
 constexpr int kWideStridedRowsMax = 4;
+constexpr int kGivenStridedRowsMax = 3;
 constexpr int kManyRows = 8192;
 constexpr size_t kSevenPerCu = 2560;  // LDS bytes that keep an eighth workgroup off a compute unit
 constexpr uint32_t kMaxDispatchItems = 0xFFFFFFFFu;  // work-items one dispatch holds (per dimension)
@@ -2859,6 +2860,13 @@ rac_status device_cus(int* cus) {
 //     and flat: 2048 x 2048 10.6 and 9.7, 4096 x 4096 34.7 and 29.1, 65536 x
 //     3584 433 and 344, 4096 x 8192 63.2 and 52.4; no outliers: 4096 x 4096
 //     28.8 and 26.9, 65536 x 3584 394 and 327.
+//   - The same with a pooled fit's pairs: strided up to kGivenStridedRowsMax,
+//     since the search for a row's segment then overlaps the row before; in the
+//     flat form each wavefront waits for its own.  us, strided and flat: 963 x
+//     4096 34.0 and 35.0 (31.4 and 33.4 where the inputs are cached), 1081 x
+//     5632 29.5 and 31.9, 1517 x 5632 42.5 and 44.3, 2634 x 3200 35.0 and 35.7;
+//     at four to five rows a workgroup 4010 x 4096 50.4 and 48.5, 4219 x 4608
+//     60.9 and 55.1.
 //   - Per-token outliers (`one`: the form that holds no next row), up to
 //     4096 channels: always one workgroup per row.  k = 8, us, strided and one
 //     per row: 2048 x 4096 18.1 and 15.8, 4096 x 4096 31.0 and 30.4, 16384 x
@@ -2890,9 +2898,11 @@ rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0,
     if (staged) threads = A.nch * kWave;
     size_t lds = staged ? (size_t)A.nch * kSlice * sizeof(float4) : 0;
     int64_t blocks = rows <= 0 ? 1 : rows;
-    const bool strided = A.launch_shape == 1;  // asked for: fn, also where each of its workgroups gets one row
+    // fn, also where each of its workgroups gets one row: asked for, or pooled
+    bool strided = A.launch_shape == 1;
     int strided_max = kStridedRowsMax;
-    if (k.one) strided_max = !k.flat && A.nch > 2 * kRowsWaves ? kWideStridedRowsMax : 0;
+    if (k.one) strided_max = k.flat ? (A.cf_given ? kGivenStridedRowsMax : 0)
+                                    : (A.nch > 2 * kRowsWaves ? kWideStridedRowsMax : 0);
     if (rows > 256 && A.launch_shape != 2 && (strided_max > 0 || strided)) {
         int cus = 0, per_cu = 0;
         if (resident(reinterpret_cast<const void*>(fn), threads, lds, &cus, &per_cu) != RAC_OK) return RAC_ERR_HIP;
@@ -2905,6 +2915,7 @@ rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0,
             const int64_t gather_min = (rows + kMaxGatherRows - 1) / kMaxGatherRows;
             if (A.ref_rows && resident < gather_min) resident = gather_min;
             if (blocks > resident) blocks = resident;
+            strided |= A.cf_given != 0;
         }
     }
     // A dispatch holds fewer than 2^32 work-items per dimension: beyond that

@@ -56,3 +56,20 @@ def test_strided_hint_takes_the_strided_kernel_at_any_row_count(record, d, k, fl
     for T, (l,) in zip(rows, per_row):
         assert l.kernel.startswith(kernel) and l.kernel.endswith(", true>")
         assert l.grid == (T if form == "rows" else -(-T * -(-d // 512) // 4))
+
+
+@pytest.mark.parametrize("d", [512, 2560, 4096, 8192])
+@pytest.mark.parametrize("k,flags", [(0, 0), (2, GRP)])
+def test_pooled_encode_strides_up_to_three_rows_a_workgroup(record, d, k, flags):
+    # (moments, merge, encode) with pairs given per segment; every other encode
+    # of these shapes takes (row, chunk) wavefronts
+    nch = -(-d // 512)
+    fits = CUS * (WAVES // nch)
+    rows = [256, 257, 3 * fits, 3 * fits + 1]
+    flat = lambda T: (True, -(-T * nch // 4))
+    got = record([("pooled", [T, d, 64, 64, 4, k, flags]) for T in rows])
+    assert [len(ls) for ls in got] == [3] * len(rows)
+    assert [(ls[2].kernel.endswith(", true>"), ls[2].grid) for ls in got] == \
+        [flat(256), (False, min(257, fits)), (False, fits), flat(3 * fits + 1)]
+    got = record([("encode", [T, d, 64, 64, 4, k, flags]) for T in rows])
+    assert [(l.kernel.endswith(", true>"), l.grid) for (l,) in got] == [flat(T) for T in rows]
