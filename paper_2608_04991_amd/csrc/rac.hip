@@ -57,8 +57,13 @@ constexpr int kFlatWaves = 4;      // wavefronts per workgroup where each takes 
 constexpr int kStridedRowsMax = 6;
 constexpr int kWideStridedRowsMax = 4;
 constexpr int kGivenStridedRowsMax = 3;
-constexpr int kManyRows = 8192;
-constexpr size_t kSevenPerCu = 2560;  // LDS bytes that keep an eighth workgroup off a compute unit
+// Where seven workgroups a compute unit are faster than eight (see launch), and
+// the LDS bytes that keep the eighth off
+constexpr int kManyRows = 16384;
+constexpr int kManyRowsMinD = 3584;
+constexpr int kManyRowsMaxK = 8;
+constexpr size_t kSevenPerCu = 2560;
+constexpr size_t kLdsPerCu = 160 << 10, kLdsGranule = 1280;
 constexpr uint32_t kMaxDispatchItems = 0xFFFFFFFFu;  // work-items one dispatch holds (per dimension)
 constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: adding it rounds to an integer (RNE)
 // The product E * r, r = v_rcp_f32(s), is rounded to an integer; products whose
@@ -1435,6 +1440,15 @@ struct RowCounters {
     uint32_t cnt[2];  // candidate count (LDS atomic), by row parity
     uint32_t xn[2];   // count of the rebuilt list (exact search), by row parity
 };
+// (the one-row form of two chunks a wavefront with k <= kTop1, whose occupancy
+// the launch lowers)
+constexpr size_t kOneRowLds =
+    sizeof(GroupShared<kRowsWaves, kCandCap, 1, false>) + sizeof(float4) * kRowsWaves * 2 * kSlice;
+constexpr size_t lds_taken(size_t bytes) { return (bytes + kLdsGranule - 1) / kLdsGranule * kLdsGranule; }
+static_assert(kManyRowsMaxK <= kTop1 && 8 * lds_taken(kOneRowLds) <= kLdsPerCu &&
+                  8 * lds_taken(kOneRowLds + kSevenPerCu) > kLdsPerCu &&
+                  7 * lds_taken(kOneRowLds + kSevenPerCu) <= kLdsPerCu,
+              "kSevenPerCu keeps exactly the eighth workgroup off a compute unit");
 static_assert(sizeof(RowCounters) <= sizeof(float4) * (kPlane - kWave), "the counters fit in a slice's gap");
 static_assert(sizeof(uint64_t) * kCandCap + sizeof(uint32_t) * kCandCap >= 3 * kWave * sizeof(uint32_t),
               "the histograms of the exact search fit in ckey and cval");
@@ -2874,10 +2888,16 @@ rac_status device_cus(int* cus) {
 //   - Wider rows (four chunks a wavefront, half as many workgroups resident):
 //     strided up to kWideStridedRowsMax.  2048 x 8192 30.6 and 31.6, 4096 x
 //     8192 57.0 and 57.8, 6144 x 8192 83.3 and 81.2.
-//   - Over kManyRows rows of more than 2048 channels with k <= kTop1, seven
-//     workgroups a compute unit instead of eight, by LDS that is requested and
-//     not used: 65536 x 3584 339.8 against 350.6 us, 32768 x 4096 194.8
-//     against 197.5 (32768 x 2048, which stays at eight, 109.2 against 107.1).
+//   - Over kManyRows rows of at least kManyRowsMinD channels, against a
+//     reference and with an fp32 reconstruction (30 KB and more a row), k <=
+//     kManyRowsMaxK: seven workgroups a compute unit instead of eight, by LDS
+//     that is requested and not used.  us, seven and eight: 24576 x 3584 131.1
+//     and 131.7, 49152 x 3584 255.4 and 265.9, 65536 x 3584 342.6 and 357.3, x
+//     4096 386.4 and 390.5, 79588 x 3712 433.5 and 445.6, 46545 x 3840 255.8
+//     and 257.1.  Outside eight are faster: fewer channels (32768 x 3328 169.4
+//     and 162.4), bf16 (65536 x 3584 290.4 and 282.3), no reference (20182 x
+//     3712 99.2 and 93.6), k = 16 (65536 x 3584 356.2 and 348.4), fewer rows
+//     (16384 x 3584 with k = 8 95.8 and 95.0).
 //   - The decode: strided up to kStridedRowsMax.  At three to six rows a
 //     resident workgroup, one per row is a few percent faster where the fp32
 //     output and a reference make the call a stream (4916 x 3072 20.6 us
@@ -2936,7 +2956,9 @@ rac_status launch(const Kernels& k, Args A, hipStream_t stream, int threads = 0,
         }
     } else if (one) {
         fn = k.one;
-        if (rows > kManyRows && A.k <= kTop1 && A.nch > kRowsWaves && A.nch <= 2 * kRowsWaves) lds = kSevenPerCu;
+        if (rows > kManyRows && A.k <= kManyRowsMaxK && A.d >= kManyRowsMinD && A.nch <= 2 * kRowsWaves && A.ref &&
+            A.xhat && !A.xhat_bf16)
+            lds = kSevenPerCu;
     }
     void* args[] = {&A};
     const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)blocks),

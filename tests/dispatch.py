@@ -30,8 +30,8 @@ for kind, arg in json.load(sys.stdin):
     else:
         c = rac.RacConfig(*arg)
         n = rac.rac_wire_size(c)
-        if kind == "encode":
-            rac.rac_encode(c, P, P, P if c.flags & 1 else None, P, P, 0, n)
+        if kind in ("encode", "encode_zero"):
+            rac.rac_encode(c, P, P if kind == "encode" else None, P if c.flags & 1 else None, P, P, 0, n)
         elif kind == "pooled":
             rac.rac_encode_pooled(c, P, P, P, None, P, P, 0, segments=5, wire_cap=n)
         elif kind == "decode":
@@ -50,8 +50,8 @@ class Launch(NamedTuple):
 
 
 def launches(calls, tmp) -> list[list[Launch]]:
-    """The launches of each call: ("encode" | "decode" | "pooled", RacConfig
-    fields), ("predictor", PredictorConfig fields + [batch]) or ("calibrate",
+    """The launches of each call: ("encode" | "encode_zero" (no reference) |
+    "decode" | "pooled", RacConfig fields), ("predictor", PredictorConfig fields + [batch]) or ("calibrate",
     list of RacConfig fields)."""
     so = os.path.join(str(tmp), "hip_recorder.so")
     if not os.path.exists(so):

@@ -73,3 +73,13 @@ def test_pooled_encode_strides_up_to_three_rows_a_workgroup(record, d, k, flags)
         [flat(256), (False, min(257, fits)), (False, fits), flat(3 * fits + 1)]
     got = record([("encode", [T, d, 64, 64, 4, k, flags]) for T in rows])
     assert [(l.kernel.endswith(", true>"), l.grid) for (l,) in got] == [flat(T) for T in rows]
+
+
+@pytest.mark.parametrize("T,d,k,flags,zero_ref,seven", [
+    (16385, 3584, 8, 0, False, True), (65536, 3584, 4, 0, False, True), (30000, 4096, 1, 0, False, True),
+    (16384, 3584, 8, 0, False, False), (65536, 3520, 4, 0, False, False), (65536, 3584, 9, 0, False, False),
+    (65536, 3584, 4, BF16, False, False), (65536, 3584, 4, 0, True, False), (65536, 4160, 4, 0, False, False),
+    (8193, 2560, 4, 0, False, False), (32768, 4096, 16, 0, False, False)])
+def test_seven_workgroups_a_compute_unit_only_where_they_are_faster(record, T, d, k, flags, zero_ref, seven):
+    ((l,),) = record([("encode_zero" if zero_ref else "encode", [T, d, 64, 64, 4, k, flags])])
+    assert l.kernel.endswith(", true>") and l.grid == T and (l.lds > 0) == seven
