@@ -1398,6 +1398,19 @@ constexpr int kKeyChBits = 13;               // channel bits of the exact search
 constexpr int kTop1 = 16;  // largest k whose first threshold comes from one maximum per lane
 constexpr int kTop2 = 48;  // largest k whose first threshold takes two per wavefront lane (beyond: four)
 
+// The candidates' keys, |E| bits << 32 | (0xFFFF - channel), which are read in
+// pairs of 16 bytes, and E bits.  Contiguous: the exact search's three 64-bin
+// histograms run from ckey into cval while the list is dropped.
+template <int CAP>
+struct alignas(16) CandList {
+    uint64_t ckey[CAP];
+    uint32_t cval[CAP];
+};
+static_assert(alignof(CandList<kCandCap>) == 16 && offsetof(CandList<kCandCap>, ckey) == 0 &&
+                  offsetof(CandList<kCandCap>, cval) == sizeof(uint64_t) * kCandCap &&
+                  sizeof(CandList<kCandCap>) >= 3 * kWave * sizeof(uint32_t),
+              "the histograms of the exact search fit in ckey and cval, with no gap between them");
+
 // The second largest |E| of each (wavefront, lane) (k > kTop1), and the third
 // and fourth, kept only with the larger candidate list.
 template <int NW, int MAXES>
@@ -1425,13 +1438,9 @@ struct CandCoef<CAP, false> {};
 // kernel's LDS is at most 20480 bytes, an eighth of a compute unit's: eight
 // workgroups a unit, 2048 on the chip.)
 template <int NW, int CAP, int MAXES, bool COEF>
-struct alignas(16) GroupShared : LaneMaxMore<NW, MAXES>, CandCoef<CAP, COEF> {
+struct alignas(16) GroupShared : CandList<CAP>, LaneMaxMore<NW, MAXES>, CandCoef<CAP, COEF> {
     static constexpr int cap = CAP;  // candidate list capacity
-    // (ckey and cval, contiguous, also hold the exact search's three
-    // 64-bin histograms while the list is dropped)
-    uint64_t ckey[CAP];  // candidates: |E| bits << 32 | (0xFFFF - channel)
-    uint32_t cval[CAP];  // their E bits
-    uint32_t crw[CAP];   // their ref word (the bf16 pair holding the channel), or R~ itself (ONE)
+    uint32_t crw[CAP];   // the candidates' ref word (the bf16 pair holding the channel), or R~ itself (ONE)
     uint32_t smax[NW][kWave]; // lane maxima of |E| of each wavefront
 };
 // A row's counters, kept in the gap between the two planes of the first slice.
@@ -1450,8 +1459,6 @@ static_assert(kManyRowsMaxK <= kTop1 && 8 * lds_taken(kOneRowLds) <= kLdsPerCu &
                   7 * lds_taken(kOneRowLds + kSevenPerCu) <= kLdsPerCu,
               "kSevenPerCu keeps exactly the eighth workgroup off a compute unit");
 static_assert(sizeof(RowCounters) <= sizeof(float4) * (kPlane - kWave), "the counters fit in a slice's gap");
-static_assert(sizeof(uint64_t) * kCandCap + sizeof(uint32_t) * kCandCap >= 3 * kWave * sizeof(uint32_t),
-              "the histograms of the exact search fit in ckey and cval");
 
 // Append this lane's elements of one chunk whose |E| pattern is >= lo (and,
 // with use_key, whose key is >= kmin) to the shared candidate list, with
