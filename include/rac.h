@@ -332,10 +332,10 @@ size_t rac_calibrate_workspace(const rac_candidate* candidates, int32_t n);
 /* Offline calibration over n candidates (HOST array, filled in place) on the
  * sample x against ref (DEVICE bf16 [tokens][hidden]; ref NULL = zero
  * reference): for each candidate, the error of rac_encode's fused
- * reconstruction as rac_recon_error measures it (candidates whose groups lie
- * inside 512 channels, without outliers or with per-group ones, are measured
- * in one pass without writing a wire or a reconstruction, the sums in another
- * fixed order); then the choice above, written to *chosen (a host int).  workspace: DEVICE memory of
+ * reconstruction as rac_recon_error measures it (two or more candidates whose
+ * groups lie inside 512 channels, without outliers or with per-group ones, are
+ * measured in one pass without writing a wire or a reconstruction, the sums in
+ * another fixed order); then the choice above, written to *chosen (a host int).  workspace: DEVICE memory of
  * rac_calibrate_workspace() bytes, 256-byte aligned.  Unlike every other
  * entry point, this offline routine reads its results back: it copies them
  * to the host and synchronizes `stream` before returning.  Argument errors

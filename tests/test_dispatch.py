@@ -83,3 +83,14 @@ def test_pooled_encode_strides_up_to_three_rows_a_workgroup(record, d, k, flags)
 def test_seven_workgroups_a_compute_unit_only_where_they_are_faster(record, T, d, k, flags, zero_ref, seven):
     ((l,),) = record([("encode_zero" if zero_ref else "encode", [T, d, 64, 64, 4, k, flags])])
     assert l.kernel.endswith(", true>") and l.grid == T and (l.lds > 0) == seven
+
+
+@pytest.mark.parametrize("T,d", [(1, 512), (34, 1280), (1538, 1024), (254, 6400)])
+def test_calibration_of_one_candidate_encodes_it(record, T, d):
+    # the pass that measures many candidates at once is the slower one for a
+    # single candidate; per-token outliers are never measured by it
+    one, other, token = [T, d, 64, 64, 4, 0, 0], [T, d, 128, 128, 4, 2, GRP], [T, d, 64, 64, 4, 8, 0]
+    got = record([("calibrate", cs) for cs in ([one], [one, token], [one, other], [one, token, other])])
+    evals = [sum(l.kernel == "rac_eval_kernel" for l in ls) for ls in got]
+    encodes = [sum("rac_encode" in l.kernel for l in ls) for ls in got]
+    assert (evals, encodes) == ([0, 0, 1, 1], [1, 2, 0, 1])
