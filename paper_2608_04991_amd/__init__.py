@@ -230,22 +230,32 @@ def _nbytes(t) -> int:
     return t.numel() * t.element_size()
 
 
-_torch = None
+_current_stream = None
+
+
+def _stream_reader(torch):
+    """A function that reads the current stream's handle.  The small calls are
+    bound by the host: building the Stream object of
+    torch.cuda.current_stream() took 2.7 us of the 8.0 us of an encode call, so
+    the raw handle is read where torch has the names it is read by (they are
+    not public; without them the Stream object serves)."""
+    public = lambda: torch.cuda.current_stream().cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return public
+    ready = torch.cuda.is_initialized
+    return lambda: raw(device()) if ready() else public()
 
 
 def _stream(stream):
-    """The HIP stream of a call: the given one, or torch's current stream.  The
-    small calls are bound by the host: building the Stream object of
-    torch.cuda.current_stream() took 2.7 us of the 8.0 us of an encode call, so
-    its raw handle is read directly once the device is initialized."""
-    global _torch
+    """The HIP stream of a call: the given one, or torch's current stream."""
+    global _current_stream
     if stream is None:
-        if _torch is None:
+        if _current_stream is None:
             import torch
-            _torch = torch
-        if _torch.cuda.is_initialized():
-            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
-        return _torch.cuda.current_stream().cuda_stream
+            _current_stream = _stream_reader(torch)
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -386,3 +386,18 @@ def test_predictor_layout_is_the_documented_one_and_errors_are_synchronous(lib):
     assert step(w=FAKE + 16) == 2 and step(x=FAKE + 8) == 2 and step(p=FAKE + 2) == 2 and step(ws=FAKE + 64) == 2
     assert step(cap=rac.rac_predictor_workspace_bytes(cfg) - 1) == 3
     assert step(B=0, w=None, p=None) == 0      # an empty batch enqueues nothing
+
+
+@pytest.mark.parametrize("missing", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",)])
+@pytest.mark.parametrize("initialized", [True, False])
+def test_current_stream_with_and_without_the_raw_handle(missing, initialized):
+    # the raw handle is read by names of torch that are not public: without
+    # them, and before the device is initialized, the Stream object's is taken
+    import types
+    C = types.SimpleNamespace(_cuda_getCurrentRawStream=lambda dev: 100 + dev, _cuda_getDevice=lambda: 3)
+    for name in missing:
+        delattr(C, name)
+    cuda = types.SimpleNamespace(is_initialized=lambda: initialized,
+                                 current_stream=lambda: types.SimpleNamespace(cuda_stream=7))
+    read = rac._stream_reader(types.SimpleNamespace(_C=C, cuda=cuda))
+    assert read() == (103 if initialized and not missing else 7)
