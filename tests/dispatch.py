@@ -14,12 +14,16 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 _CHILD = r"""
 import ctypes, json, sys
 rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
-rec.recorded.restype = ctypes.c_char_p
+rec.recorded.restype = rec.registered.restype = ctypes.c_char_p
 import paper_2608_04991_amd as rac
 P = 1 << 20  # a stand-in for every device pointer (aligned; nothing reads it)
 out = []
 for kind, arg in json.load(sys.stdin):
     rec.forget()
+    if kind == "all":
+        rac.library()
+        out.append(rec.registered().decode())
+        continue
     if kind == "predictor":
         *cfg, batch = arg
         c = rac.PredictorConfig(*cfg)
@@ -52,7 +56,7 @@ class Launch(NamedTuple):
 def launches(calls, tmp) -> list[list[Launch]]:
     """The launches of each call: ("encode" | "encode_zero" (no reference) |
     "decode" | "pooled", RacConfig fields), ("predictor", PredictorConfig fields + [batch]) or ("calibrate",
-    list of RacConfig fields)."""
+    list of RacConfig fields).  ("all", None) gives every kernel of the library."""
     so = os.path.join(str(tmp), "hip_recorder.so")
     if not os.path.exists(so):
         subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "hip_recorder.cpp")],

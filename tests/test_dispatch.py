@@ -94,3 +94,15 @@ def test_calibration_of_one_candidate_encodes_it(record, T, d):
     evals = [sum(l.kernel == "rac_eval_kernel" for l in ls) for ls in got]
     encodes = [sum("rac_encode" in l.kernel for l in ls) for ls in got]
     assert (evals, encodes) == ([0, 0, 1, 1], [1, 2, 0, 1])
+
+
+def test_every_predictor_kernel_is_run_by_a_gpu_test(record):
+    from tests import test_gpu_predictor as G
+    shapes = list(G.EVERY_KERNEL)
+    for f in (G.test_predictor_product_tiles, G.test_predictor_small_batches_fold_the_norms):
+        shapes += next(m for m in f.pytestmark if m.name == "parametrize").args[1]
+    shapes += [(4096, 512, 8, 2048, 64, b) for b in (1, 100, 256)] + [(512, 128, 2, 256, w, 8) for w in (300, 1024)]
+    every, *got = record([("all", None)] + [("predictor", [*s[:5], 256, s[5]]) for s in shapes])
+    kernels = {l.kernel for l in every if l.kernel.startswith("pred_")}
+    assert len(kernels) >= 27
+    assert kernels - {l.kernel for ls in got for l in ls} == set()

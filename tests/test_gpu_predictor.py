@@ -94,7 +94,7 @@ def test_predictor_ragged_batch_with_staggered_and_restarted_positions():
 
 @pytest.mark.parametrize("batch", [1, 100, 256])
 def test_predictor_single_and_full_batches(batch):
-    # (100: the wide products with a ragged second tile of 64 rows)
+    # (100: ragged row tiles, 6 x 16 + 4 and 3 x 32 + 4)
     cfg = rac.PredictorConfig(4096, 512, 8, 2048, 64, 256)
     say(f"[gpu] predictor batch {batch}, 3 steps")
     _run(cfg, batch, 3, lambda s, b: s + 100 * (b % 2), seed=1)
@@ -115,9 +115,9 @@ def test_predictor_windows_longer_than_one_pass_of_64_positions(window, start):
     (4096, 512, 8, 2048, 64, 2), (4096, 512, 8, 2048, 64, 4),
     (1024, 2048, 32, 512, 16, 3), (512, 128, 2, 256, 5, 4)])
 def test_predictor_small_batches_fold_the_norms(hidden, model, heads, ffn, window, batch):
-    # batches of at most four rows form each norm inside the product that
-    # consumes it; widths 128 to 2048, including a down projection of one
-    # K range (ffn 256 and 512)
+    # a few rows in the smallest tiles, whose products form the norm of what
+    # they read; model widths 128 to 2048, and down projections of 4, 8 and 32
+    # units of 64 channels over eight wavefronts
     cfg = rac.PredictorConfig(hidden, model, heads, ffn, window, 4)
     say(f"[gpu] predictor {hidden}/{model}/{heads}/{ffn}, window {window}, batch {batch}, 6 steps")
     _run(cfg, batch, 6, lambda s, b: s + 3 * b, seed=4)
@@ -127,10 +127,27 @@ def test_predictor_small_batches_fold_the_norms(hidden, model, heads, ffn, windo
     (512, 2048, 32, 256, 3, 33), (8192, 128, 2, 8192, 5, 1), (512, 2048, 32, 128, 2, 130),
     (8192, 1536, 24, 8192, 3, 75), (2048, 2048, 32, 4096, 2, 60)])
 def test_predictor_product_tiles(hidden, model, heads, ffn, window, batch):
-    # every tile of the products with a ragged last row tile (33 = 2 x 16 + 1
+    # tiles of the products with a ragged last row tile (33 = 2 x 16 + 1
     # and 32 + 1; 130 = 4 x 32 + 2; 1), and K shares from none at all (two
     # units of 64 channels over eight wavefronts) to sixteen units; the last
     # three also take products whose rows are normalized ahead of them
     cfg = rac.PredictorConfig(hidden, model, heads, ffn, window, batch)
     say(f"[gpu] predictor {hidden}/{model}/{heads}/{ffn}, window {window}, batch {batch}, 3 steps")
     _run(cfg, batch, 3, lambda s, b: s + b % 4, seed=5)
+
+
+# With the shapes above every kernel of the predictor (tests/test_dispatch.py
+# holds the library to that): each tile of each product, rows normalized on the
+# way and ahead, and the attention's one, two and four wavefronts, the two at
+# both ends of their windows (66 and 129)
+EVERY_KERNEL = [
+    (8192, 1024, 16, 4096, 66, 16), (8192, 1024, 16, 4096, 100, 250), (512, 2048, 32, 128, 129, 32),
+    (8192, 128, 2, 128, 3, 32), (512, 1536, 24, 128, 2, 130)]
+
+
+@pytest.mark.parametrize("hidden,model,heads,ffn,window,batch", EVERY_KERNEL)
+def test_predictor_every_kernel(hidden, model, heads, ffn, window, batch):
+    # positions from inside the first window to past its second turn
+    cfg = rac.PredictorConfig(hidden, model, heads, ffn, window, batch)
+    say(f"[gpu] predictor {hidden}/{model}/{heads}/{ffn}, window {window}, batch {batch}, 3 steps")
+    _run(cfg, batch, 3, lambda s, b: s + (2 * window * b) // max(1, batch - 1) if batch > 1 else s, seed=6)
