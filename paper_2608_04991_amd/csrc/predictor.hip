@@ -121,8 +121,18 @@ struct ProdUnit {
     u32x2 g;
 };
 
+// Accuracy: the matrix core rounds more than once within an instruction, so the
+// error of a sum grows with the chain of instructions on one accumulator.  The
+// products onto the model width, whose K reaches 8192, take a new accumulator
+// for every unit, add it in fp32 to one of two sums, and add the eight
+// wavefronts' sums pairwise.  The error of sums that cancel to 2^-18 of their
+// terms' scale, relative to fp32 chains of 128 channels added in order: 1.14 at
+// K = 2048, 1.15 at 4096 and 1.18 at 8192; with one accumulator over a
+// wavefront's K 1.5, 2.0 and 2.5.  The sums cost 0.2% of a step on average.
 template <int TM, int TN, int KW, int Q, int EPI, bool NORM, int COLS = 16>
 __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
+    constexpr bool kSums = EPI == kHidden;      // a new accumulator every unit, two sums
+    constexpr int U = kSums && Q == 1 ? 2 : Q;  // units a round of the loop
     constexpr int WI = COLS / 8;  // eights of weight rows loaded per column tile
     constexpr int F = TM * TN, FPW = (F + KW - 1) / KW;
     constexpr int kBlk = 128;  // 16-byte slots per block of 16 rows x 64 channels
@@ -223,9 +233,12 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
             for (int i = 0; i < 4; ++i) inv[r][i] = __shfl(iv, 16 * i + 4 * (int)lq);
         }
     }
-    f32x4 acc[F];
+    f32x4 acc[kSums ? 2 : 1][F];
 #pragma unroll
-    for (int f = 0; f < F; ++f) acc[f] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int f = 0; f < F; ++f) {
+        acc[0][f] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (kSums) acc[1][f] = acc[0][f];
+    }
     auto put = [&](const ProdUnit<TM, TN, NORM>& b) {
         const uint32_t c = lane & 7u, r8 = lane >> 3;
 #pragma unroll
@@ -254,7 +267,13 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
             }
         }
     };
-    auto product = [&]() {
+    auto product = [&](int i) {  // (unit i of a round)
+        f32x4* const into = acc[kSums ? i % 2 : 0];
+        f32x4 sum[kSums ? F : 1];
+        if constexpr (kSums) {
+#pragma unroll
+            for (int f = 0; f < F; ++f) sum[f] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
         wave_sync();
 #pragma unroll
         for (uint32_t step = 0; step < 2u; ++step) {
@@ -267,41 +286,56 @@ __global__ __launch_bounds__(kW * KW) void pred_prod(Prod p) {
 #pragma unroll
             for (int r = 0; r < TM; ++r)
 #pragma unroll
-                for (int t = 0; t < TN; ++t)
-                    acc[r * TN + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[t], av[r], acc[r * TN + t], 0, 0, 0);
+                for (int t = 0; t < TN; ++t) {
+                    f32x4& c = kSums ? sum[r * TN + t] : into[r * TN + t];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[t], av[r], c, 0, 0, 0);
+                }
         }
         wave_sync();
+        if constexpr (kSums) {
+#pragma unroll
+            for (int f = 0; f < F; ++f) into[f] = into[f] + sum[f];
+        }
     };
     int u = 0;
-    for (; u + 2 * Q <= nu; u += Q) {
+    for (; u + U + Q <= nu; u += U) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            put(st[i]);
-            load(st[i], u + Q + i);
-            product();
+        for (int i = 0; i < U; ++i) {
+            put(st[i % Q]);
+            load(st[i % Q], u + Q + i);
+            product(i);
         }
     }
-    for (; u < nu; u += Q) {
+    for (; u < nu; u += U) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
+        for (int i = 0; i < U; ++i) {
             if (u + i < nu) {
-                put(st[i]);
-                if (u + Q + i < nu) load(st[i], u + Q + i);
-                product();
+                put(st[i % Q]);
+                if (u + Q + i < nu) load(st[i % Q], u + Q + i);
+                product(i);
             }
         }
     }
+    if constexpr (kSums) {
+#pragma unroll
+        for (int f = 0; f < F; ++f) acc[0][f] = acc[0][f] + acc[1][f];
+    }
     // the wavefronts' sums, through each one's own slice
 #pragma unroll
-    for (int f = 0; f < F; ++f) reinterpret_cast<f32x4*>(mine)[f * kW + lane] = acc[f];
+    for (int f = 0; f < F; ++f) reinterpret_cast<f32x4*>(mine)[f * kW + lane] = acc[0][f];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < FPW; ++i) {
         const int f = w + i * KW;
         if (f >= F) return;
-        f32x4 v = reinterpret_cast<const f32x4*>(stage[0])[f * kW + lane];
-#pragma unroll
-        for (int x = 1; x < KW; ++x) v = v + reinterpret_cast<const f32x4*>(stage[x])[f * kW + lane];
+        auto sum = [&](int x) { return reinterpret_cast<const f32x4*>(stage[x])[f * kW + lane]; };
+        f32x4 v;
+        if constexpr (KW == 8) {
+            v = ((sum(0) + sum(1)) + (sum(2) + sum(3))) + ((sum(4) + sum(5)) + (sum(6) + sum(7)));
+        } else {
+            static_assert(KW == 4, "four or eight wavefronts");
+            v = ((sum(0) + sum(1)) + sum(2)) + sum(3);
+        }
         const int row = m0 + 16 * (f / TN) + (int)lr, col = n0 + COLS * (f % TN) + 4 * (int)lq;
         const bool in = row < p.M && 4 * (int)lq < COLS;
         if constexpr (EPI == kHidden) {

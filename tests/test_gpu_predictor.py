@@ -151,3 +151,64 @@ def test_predictor_every_kernel(hidden, model, heads, ffn, window, batch):
     cfg = rac.PredictorConfig(hidden, model, heads, ffn, window, batch)
     say(f"[gpu] predictor {hidden}/{model}/{heads}/{ffn}, window {window}, batch {batch}, 3 steps")
     _run(cfg, batch, 3, lambda s, b: s + (2 * window * b) // max(1, batch - 1) if batch > 1 else s, seed=6)
+
+
+@pytest.mark.parametrize("hidden,model,batch", [
+    (2048, 128, 64), (8192, 128, 64), (8192, 512, 80), (8192, 1024, 100), (8192, 1024, 250), (4096, 2048, 160)])
+def test_predictor_products_onto_the_model_width_keep_their_accuracy(hidden, model, batch):
+    """The fp32 error of h0 = x W_in^T, made visible: the channels come in pairs
+    with x equal and W_in opposite, at random places, so a sum cancels to the
+    one signal of 2^-18 and what else is left of it is rounding error.  W_o and
+    W_down are zero, the gains one and W_out passes the model width through to
+    channels where x is zero, so R there is RMSNorm(h0): a signal common to the
+    row with the errors around it, about 2^-6 of it, well over bf16's 2^-9.
+
+    The bar is a simulation of fp32 sums in chains of 128 channels, each 32 of
+    them added exactly, four chains and then the ranges of 512 in order, times
+    1.35: the matrix core rounds inside its 32 channels as well, with which such
+    chains measured 1.0 to 1.3 of the simulation for these shapes.  One
+    accumulator over the channels of a wavefront measures 1.5 to 2.6."""
+    import torch
+    say(f"[gpu] predictor accuracy {hidden}/{model}, batch {batch}")
+    signal = 2.0 ** -18
+    rng = np.random.default_rng([hidden, model, batch])
+    half = (hidden - model) // 2
+    to_bf = lambda a: wl.f32_to_bf16_bits(np.asarray(a, np.float32))
+    rounded = lambda a: wl.bf16_bits_to_f32(to_bf(a))
+    x, w = np.zeros((batch, hidden), np.float32), np.zeros((model, hidden), np.float32)
+    place = model + rng.permutation(2 * half)
+    a, b = place[:half], place[half:]
+    x[:, a] = x[:, b] = rounded(rng.standard_normal((batch, half)))
+    w[:, a] = rounded(rng.standard_normal((model, half)) / np.sqrt(2 * half))
+    w[:, b] = -w[:, a]
+    x[:, a[0]], w[:, a[0]], w[:, b[0]] = 1.0, signal, 0.0
+    through = np.zeros((hidden, model), np.float32)
+    through[np.arange(model), np.arange(model)] = 1.0
+    zero, one = (lambda *s: np.zeros(s, np.uint16)), to_bf(np.ones(model))
+    weights = dict(w_in=to_bf(w), g1=one, w_qkv=zero(3 * model, model), w_o=zero(model, model), g2=one,
+                   w_gu=zero(256, model), w_down=zero(model, 128), g3=one, w_out=to_bf(through))
+    cfg = rac.PredictorConfig(hidden, model, model // 64, 128, 4, batch)
+    blob = torch.from_numpy(rac.predictor_pack(cfg, weights)).cuda()
+    cache = torch.zeros(rac.rac_predictor_cache_bytes(cfg) // 2, dtype=torch.int16, device="cuda")
+    ws = torch.empty(rac.rac_predictor_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    out = torch.empty(batch, hidden, dtype=torch.int16, device="cuda")
+    rac.rac_predictor_step(cfg, blob, cache, torch.zeros(batch, dtype=torch.int32, device="cuda"),
+                           torch.from_numpy(to_bf(x).view(np.int16)).cuda(), out, ws, batch)
+    torch.cuda.synchronize()
+    r = P.bf16_to_f64(out.cpu().numpy().view(np.uint16))[:, :model]
+    err = np.sqrt(np.mean((signal * (r / r.mean(1, keepdims=True) - 1.0)) ** 2))
+    rows = x[:max(2, 4096 // model)].astype(np.float64).reshape(-1, 1, hidden // 32, 32)
+    dots = np.stack([(r * w.astype(np.float64).reshape(model, hidden // 32, 32)).sum(-1) for r in rows])
+    add = lambda s, v: (s + v).astype(np.float32).astype(np.float64)
+    total = 0.0
+    for k in range(0, hidden // 32, 16):
+        chains = []
+        for q in range(k, k + 16, 4):
+            c = add(0.0, dots[..., q])
+            for i in range(q + 1, q + 4):
+                c = add(c, dots[..., i])
+            chains.append(c)
+        total = add(total, add(add(add(chains[0], chains[1]), chains[2]), chains[3]))
+    bar = np.sqrt(np.mean((total - signal) ** 2))
+    say(f"[gpu]   error {err:.3e}, chains of 128 {bar:.3e} ({err / bar:.2f})")
+    assert err <= 1.35 * bar
