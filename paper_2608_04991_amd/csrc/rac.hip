@@ -2880,7 +2880,10 @@ rac_status device_cus(int* cus) {
 //     always a (row, chunk) per wavefront, in row order.  k_g = 2, us, strided
 //     and flat: 2048 x 2048 10.6 and 9.7, 4096 x 4096 34.7 and 29.1, 65536 x
 //     3584 433 and 344, 4096 x 8192 63.2 and 52.4; no outliers: 4096 x 4096
-//     28.8 and 26.9, 65536 x 3584 394 and 327.
+//     28.8 and 26.9, 65536 x 3584 394 and 327.  (With no outliers, up to two
+//     and a half rows a resident workgroup and inputs that are in no cache, all
+//     rows at once cost up to 14%: 1246 x 2816 8.8 us against 7.7 with fewer in
+//     flight; cached, 5.6 against 5.8.)
 //   - The same with a pooled fit's pairs: strided up to kGivenStridedRowsMax,
 //     since the search for a row's segment then overlaps the row before; in the
 //     flat form each wavefront waits for its own.  us, strided and flat: 963 x
@@ -2893,8 +2896,9 @@ rac_status device_cus(int* cus) {
 //     per row: 2048 x 4096 18.1 and 15.8, 4096 x 4096 31.0 and 30.4, 16384 x
 //     4096 110.8 and 103.6, 4096 x 2048 20.9 and 18.6.
 //   - Wider rows (four chunks a wavefront, half as many workgroups resident):
-//     strided up to kWideStridedRowsMax.  2048 x 8192 30.6 and 31.6, 4096 x
-//     8192 57.0 and 57.8, 6144 x 8192 83.3 and 81.2.
+//     strided from more than one row a workgroup up to kWideStridedRowsMax.
+//     2048 x 8192 30.6 and 31.6, 4096 x 8192 57.0 and 57.8, 6144 x 8192 83.3
+//     and 81.2.
 //   - Over kManyRows rows of at least kManyRowsMinD channels, against a
 //     reference and with an fp32 reconstruction (30 KB and more a row), k <=
 //     kManyRowsMaxK: seven workgroups a compute unit instead of eight, by LDS
