@@ -106,3 +106,21 @@ def test_every_predictor_kernel_is_run_by_a_gpu_test(record):
     kernels = {l.kernel for l in every if l.kernel.startswith("pred_")}
     assert len(kernels) >= 27
     assert kernels - {l.kernel for ls in got for l in ls} == set()
+
+
+def test_every_form_of_the_rows_kernel_is_run_by_a_gpu_test(record):
+    import re
+    from tests import test_gpu_launch_shapes as S, test_gpu_pooled as G
+    params = lambda f: next(m for m in f.pytestmark if m.name == "parametrize").args[1]
+    calls = [(kind, [*c[:6], c[6] | hint]) for kind, f in (("encode", S.test_strided_form_takes_several_rows),
+                                                          ("pooled", G.test_pooled_forms_and_launch_shapes))
+             for c in params(f) for hint in (0, STRIDED, PER_ROW)]
+    fields = lambda c: [c[n] for n in ("tokens", "hidden", "group_align", "group_quant", "bits", "outlier_k")]
+    calls += [("encode", [*fields(c), c["flags"] | hint]) for c, _ in S.CASES.values() for hint in (0, STRIDED, PER_ROW)]
+    calls += [("pooled", [*fields(c), c["flags"]]) for c, *_ in G.CASES.values()]
+    every, *got = record([("all", None)] + calls)
+    # (wavefronts, chunks a wavefront, pooled, two-value and large-list
+    # thresholds, one row; whatever the bits and group shapes)
+    forms = lambda ls: {m.group(1) for l in ls if (m := re.match(r"rac_encode_rows_kernel<\d, -?\d, -?\d, (.*)>", l.kernel))}
+    assert len(forms(every)) == 14
+    assert forms(every) - {f for ls in got for f in forms(ls)} == set()

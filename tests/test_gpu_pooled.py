@@ -169,3 +169,20 @@ def test_pooled_with_fixed_steps_and_group_outliers():
     torch.cuda.synchronize()
     assert_parity(c, wire.cpu().numpy(), xh.cpu().numpy(), ow, ox)
     assert torch.equal(xh, xd)
+
+
+@pytest.mark.parametrize("T,d,ga,gq,bits,k,flags", [
+    (2100, 8192, 128, 128, 4, 8, 0), (1300, 5120, 64, 64, 8, 40, 0),       # four chunks a wavefront
+    (9000, 1024, 64, 128, 3, 0, 0), (12300, 1024, 128, 128, 4, 2, GRP)])   # up to three rows a workgroup, and beyond
+def test_pooled_forms_and_launch_shapes(T, d, ga, gq, bits, k, flags):
+    # the pooled encode's kernels beyond one row a workgroup, under every hint
+    rng = np.random.default_rng([T, d])
+    seg = np.unique(np.concatenate([[0, T], rng.integers(1, T, 90)])).astype(np.int32)
+    xb, rb, _ = wl.prefill_uplink(14, tokens=T, hidden=d)
+    c = cfgd(T, d, ga, gq, bits, k, flags)
+    ow, ox = _oracle_pooled(c, xb, rb, seg)
+    for hint in (0, rac.RAC_FLAG_LAUNCH_STRIDED, rac.RAC_FLAG_LAUNCH_PER_ROW):
+        say(f"[gpu] pooled forms {T}x{d} g={ga}/{gq} b={bits} k={k} flags={flags}: hint {hint}")
+        gw, gx, gd = _gpu_pooled(dict(c, flags=flags | hint), xb, rb, seg)
+        assert_parity(c, gw, gx, ow, ox)
+        assert np.array_equal(gx.view(np.uint8), gd.view(np.uint8))
